@@ -205,6 +205,18 @@ gcn_status aggregate_f32(const Mat& m, const float* X, int64_t ldx, float* Y, in
 gcn_status gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                     const float* B, int64_t ldb, float* C, int64_t ldc, hipStream_t stream,
                     const float* mask = nullptr, int64_t ldm = 0, bool relu = false);
+// The same products on the bf16 matrix cores with three-part operands
+// (gemm_split.hip), any alignment, for sizes and strides that *_takes accepts.
+bool gemm_split_tall_takes(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldc, int64_t ldm);
+bool gemm_split_tn_takes(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb);
+gcn_status gemm_split_tall(int op, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
+                           const float* B, int64_t ldb, float* C, int64_t ldc, const float* mask,
+                           int64_t ldm, bool relu, hipStream_t stream);
+gcn_status gemm_split_tn(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
+                         const float* B, int64_t ldb, float* C, int64_t ldc, hipStream_t stream);
+// C = sum over the chunks of part [chunks][M][N], in chunk order.
+gcn_status sum_partials(int64_t M, int64_t N, int64_t chunks, const float* part, float* C,
+                        int64_t ldc, hipStream_t stream);
 // Input gradient of a GraphSAGE layer whose output is narrower than its
 // input, fused with the LayerNorm backward: dY = DG B^T (DG [n x K] with
 // 16-byte aligned rows, B [F x K]), then dX = rstd (dY - mean(dY) - Y

@@ -10,13 +10,15 @@
 //    each wavefront owns 16 rows and issues v_mfma_f32_16x16x4_f32 on BN / 16
 //    blocks of 16 x 16. The tile leaves through LDS as row-contiguous
 //    16-byte stores, with an optional ReLU or ReLU-backward mask.
-//  * Products whose B fits in LDS (weights: K x 48 for the classes, K x 256
-//    slices for the hidden layer) take a resident-B kernel: B is staged once
-//    per CU and every wavefront streams its own rows of A into the
-//    matrix-core registers, several chunks ahead.
+//  * Products of at most 48 columns whose B fits in LDS (the class layer) take
+//    a resident-B kernel: B is staged once per CU and every wavefront streams
+//    its own rows of A into the matrix-core registers, several chunks ahead.
 //  * C = A^T B with K = nodes (the weight gradients): K is split into fixed
 //    chunks; every chunk writes a partial C tile and a second kernel adds the
 //    partials in chunk order, so the result is the same on every run.
+//  * Wider products, and most of the weight gradients, run on the bf16 matrix
+//    cores with three-part operands (gemm_split.hip); the kernels here take
+//    what is too small for that, and strides it does not.
 //
 // v_mfma_f32_16x16x4_f32 operand layout (lane l of the wavefront): a holds
 // A[l % 16][k0 + l / 16], b holds B[k0 + l / 16][l % 16], and result element
@@ -38,16 +40,7 @@ constexpr int kThreads = 256;
 constexpr int kTile = 64;  // C tile is kTile x kTile
 constexpr int kKc = 32;    // K slice staged in LDS
 constexpr int kPad = 1;    // LDS row padding against bank conflicts
-constexpr int64_t kSplitRows = 8192;  // K chunk of the A^T B kernel
-#ifndef GCN_TN_MIN_BLOCKS
-#define GCN_TN_MIN_BLOCKS 4096
-#endif
-#ifndef GCN_TN_MIN_SPLIT
-#define GCN_TN_MIN_SPLIT 1024
-#endif
-constexpr int64_t kSplitRowsMin = GCN_TN_MIN_SPLIT;
-constexpr int64_t kTnMinBlocks = GCN_TN_MIN_BLOCKS;  // workgroups the A^T B grid aims for
-
+constexpr int64_t kSplitRows = 8192;  // K chunk of the general A^T B kernel
 enum Op { kNN = 0, kNT = 1 };
 
 // C[M x N] = A[M x K] * B[K x N] (NN) or A[M x K] * B[N x K]^T (NT).
@@ -194,10 +187,6 @@ __device__ inline f4 load4(const float* __restrict__ p, int64_t row, int64_t row
 #ifndef GCN_GEMM_MIN_BLOCKS
 #define GCN_GEMM_MIN_BLOCKS 2
 #endif
-// From this depth on, the 256-column NN tile takes two 16-row blocks per
-// wavefront (128 x 256 per workgroup, each B fragment feeding two MFMAs):
-// 3% faster at K = 516, slower at K <= 204.
-constexpr int64_t kDeepK = 384;
 // Workgroups per CU the 64- and 128-column tiles must fit (fewer registers,
 // more waves to overlap LDS and global latency).
 #ifndef GCN_GEMM_MIN_BLOCKS_NARROW
@@ -670,66 +659,6 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_bres(
     for (int rb = 0; rb < RB; ++rb) {
       pc[rb] = pn[rb];
       pn[rb] = rowptr(tile + 2 * TW, rb);
-    }
-  }
-}
-
-// Wide-tile partial C = A^T B over one K chunk for 16-byte aligned operands:
-// a (16 * WAVES) x BN tile per workgroup, so for C up to 128 x 256 each row
-// of A and B is read once per chunk.
-template <int WAVES, int BN>
-__global__ __launch_bounds__(WAVES * 64) void k_gemm_tn_v(int64_t M, int64_t N, int64_t K,
-                                                          int64_t split,
-                                                          const float* __restrict__ A, int64_t lda,
-                                                          const float* __restrict__ B, int64_t ldb,
-                                                          float* __restrict__ part) {
-  constexpr int BM = 16 * WAVES, NT = 64 * WAVES, NB = BN / 16;
-  // row strides of 16 mod 32 floats: a half-wavefront's reads (16 columns x
-  // 2 rows) hit 32 distinct banks
-  __shared__ __align__(16) float As[kKc][stride_n(BM)];
-  __shared__ __align__(16) float Bs[kKc][stride_n(BN)];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int64_t m0 = (int64_t)blockIdx.x * BM;
-  const int64_t n0 = (int64_t)blockIdx.y * BN;
-  const int64_t chunk = blockIdx.z;
-  const int64_t kb = chunk * split;
-  const int64_t ke = std::min(K, kb + split);
-  f4 acc[NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) acc[j] = f4{0.f, 0.f, 0.f, 0.f};
-  for (int64_t k0 = kb; k0 < ke; k0 += kKc) {
-#pragma unroll
-    for (int j = 0; j < kKc * BM / 4 / NT; ++j) {
-      const int idx = t + NT * j, r = idx / (BM / 4), c = (idx % (BM / 4)) * 4;
-      *reinterpret_cast<f4*>(&As[r][c]) = load4(A, k0 + r, ke, lda, m0 + c, M);
-    }
-    constexpr int BQ = kKc * BN / 4;  // 16-byte pieces of a B slice
-#pragma unroll
-    for (int j = 0; j < (BQ + NT - 1) / NT; ++j) {
-      const int idx = t + NT * j, r = idx / (BN / 4), c = (idx % (BN / 4)) * 4;
-      if (BQ % NT != 0 && idx >= BQ) continue;
-      *reinterpret_cast<f4*>(&Bs[r][c]) = load4(B, k0 + r, ke, ldb, n0 + c, N);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < kKc; kk += 4) {
-      const float a = As[kk + (lane >> 4)][16 * w + (lane & 15)];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const float b = Bs[kk + (lane >> 4)][16 * j + (lane & 15)];
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[j], 0, 0, 0);
-      }
-    }
-    __syncthreads();
-  }
-  float* out = part + chunk * M * N;
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int64_t gn = n0 + 16 * j + (lane & 15);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t gm = m0 + 16 * w + 4 * (lane >> 4) + i;
-      if (gm < M && gn < N) out[gm * N + gn] = acc[j][i];
     }
   }
 }
@@ -1642,18 +1571,11 @@ hipError_t launch_bres(int64_t M, int64_t N, int64_t K, const float* A, int64_t 
   return hipGetLastError();
 }
 
-// The resident-B kernel takes tall products whose B slice fits in LDS: 48
-// columns (the class count, 47) or 256-column slices of outputs wider than
-// 128 (the hidden layer). A ReLU-backward mask stays with the staged tile,
-// which loads the mask values before it stages the output (in the resident
-// kernel each tile would wait for them: the GCN step's dH1 took 1.46 ms
-// against 1.17).
-int resident_blocks(int64_t M, int64_t N, int64_t K, bool masked) {
-  if (!GCN_GEMM_RESIDENT || M < kResMinRows || K < 16 || masked) return 0;
-  const int nblk = N <= 48 ? 3 : (N > 128 ? 16 : 0);
-  if (nblk == 0) return 0;
-  const int64_t lds = ceil_div(K, (int64_t)16) * 16 * 16 * nblk * (int64_t)sizeof(float);
-  return lds <= kResMaxLds ? nblk : 0;
+// The resident-B kernel takes unmasked tall products of at most 48 columns
+// (the class count, 47) whose B fits in LDS.
+bool resident_fits(int64_t M, int64_t N, int64_t K, bool masked) {
+  if (!GCN_GEMM_RESIDENT || M < kResMinRows || K < 16 || N > 48 || masked) return false;
+  return ceil_div(K, (int64_t)16) * 16 * 48 * (int64_t)sizeof(float) <= kResMaxLds;
 }
 
 template <int OP>
@@ -1663,31 +1585,18 @@ hipError_t launch_tall(int64_t M, int64_t N, int64_t K, const float* A, int64_t 
   const int bn = OP == kNN ? tile_n(N) : tile_n_narrow(N);
   // staged 16-byte stores need 16-byte aligned rows of C (and of the mask)
   const bool cvec = aligned16(C, ldc) && (!mask || aligned16(mask, ldm));
-  const int nblk = resident_blocks(M, N, K, mask != nullptr);
   // ring: D slots of CPS chunks (D * CPS must divide the chunk count)
   const int64_t nc = K / 16;
 #define GCN_BRES(D_, CPS_)                                                                 \
   return launch_bres<OP, 3, 2, D_, CPS_, 8>(M, N, K, A, lda, B, ldb, C, ldc, mask, ldm, relu, \
                                             cvec, stream)
-  if (nblk == 3) {
+  if (resident_fits(M, N, K, mask != nullptr)) {
     if (nc % 8 == 0) GCN_BRES(2, 4);
     if (nc % 4 == 0) GCN_BRES(2, 2);
     if (nc % 2 == 0) GCN_BRES(2, 1);
     GCN_BRES(1, 1);
   }
 #undef GCN_BRES
-  // 256 columns: one 16-row block per wavefront (64 accumulator registers),
-  // one chunk per slot
-#define GCN_BRES16(D_)                                                                      \
-  return launch_bres<OP, 16, 1, D_, 1, 8>(M, N, K, A, lda, B, ldb, C, ldc, mask, ldm, relu, \
-                                          cvec, stream)
-  if (nblk == 16) {
-    if (nc % 4 == 0) GCN_BRES16(4);
-    if (nc % 3 == 0) GCN_BRES16(3);
-    if (nc % 2 == 0) GCN_BRES16(2);
-    GCN_BRES16(1);
-  }
-#undef GCN_BRES16
   const dim3 grid((unsigned)ceil_div(M, kTile), (unsigned)ceil_div(N, bn));
   if (bn == 48) {  // two 16-row blocks per wavefront (each B fragment feeds two MFMAs)
     const dim3 grid2((unsigned)ceil_div(M, (int64_t)kTile * 2), (unsigned)ceil_div(N, bn));
@@ -1700,50 +1609,12 @@ hipError_t launch_tall(int64_t M, int64_t N, int64_t K, const float* A, int64_t 
   else if (OP != kNN || bn == 128)
     hipLaunchKernelGGL((k_gemm_tall_v<OP, 128, 1>), grid, dim3(kThreads), 0, stream, M, N, K, A,
                        lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
-  else if constexpr (OP == kNN) {
-    if (K >= kDeepK) {  // deep products: 128 x 256 tiles
-      const dim3 grid_w((unsigned)ceil_div(M, (int64_t)kTile * 2), (unsigned)ceil_div(N, bn));
-      hipLaunchKernelGGL((k_gemm_tall_v<OP, 256, 2>), grid_w, dim3(kThreads), 0, stream, M, N,
-                         K, A, lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
-    } else {
-      hipLaunchKernelGGL((k_gemm_tall_v<OP, 256, 1>), grid, dim3(kThreads), 0, stream, M, N, K,
-                         A, lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
-    }
-  }
+  else if constexpr (OP == kNN)
+    hipLaunchKernelGGL((k_gemm_tall_v<OP, 256, 1>), grid, dim3(kThreads), 0, stream, M, N, K, A,
+                       lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
   return hipGetLastError();
 }
 
-
-// Output tiles of at most 128 rows; the wavefront count (16 rows each) is
-// chosen so that the ceil(M / 128) tiles cover M with the least padding
-// (M = 200: two tiles of 112 rows instead of 128; M = 47: one of 48).
-void launch_tn(int64_t M, int64_t N, int64_t K, int64_t split, int64_t n_chunks, const float* A,
-               int64_t lda, const float* B, int64_t ldb, float* part, hipStream_t stream) {
-  const int64_t mb = ceil_div(M, (int64_t)16);
-  const int waves = (int)ceil_div(mb, ceil_div(mb, (int64_t)8));
-  const int bn = tile_n_narrow(N);
-  const dim3 grid((unsigned)ceil_div(M, (int64_t)16 * waves), (unsigned)ceil_div(N, bn),
-                  (unsigned)n_chunks);
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, dim3(64 * waves), 0, stream, M, N, K, split, A, lda, B, ldb,
-                       part);
-  };
-#define GCN_TNV(W_)                                        \
-  case W_:                                                 \
-    if (bn == 48)                                          \
-      go(k_gemm_tn_v<W_, 48>);                             \
-    else if (bn == 64)                                     \
-      go(k_gemm_tn_v<W_, 64>);                             \
-    else                                                   \
-      go(k_gemm_tn_v<W_, 128>);                            \
-    break
-  switch (waves) {
-    GCN_TNV(1); GCN_TNV(2); GCN_TNV(3); GCN_TNV(4);
-    GCN_TNV(5); GCN_TNV(6); GCN_TNV(7);
-    default: GCN_TNV(8);
-  }
-#undef GCN_TNV
-}
 
 // The streaming A^T B kernel: C tiles of 64 x 16 NB (N <= 64), at most 16 of
 // them (one wavefront each, up to 8 per workgroup), K cut into chunks so that
@@ -1752,7 +1623,9 @@ void launch_tn(int64_t M, int64_t N, int64_t K, int64_t split, int64_t n_chunks,
 #define GCN_GEMM_TN_STREAM 1
 #endif
 constexpr int kTnsD = 4, kTnsCps = 2;
-constexpr int64_t kTnsMinK = 65536;
+// below this the three-part kernel is at least as fast (170,003 x 100 x 64: 45 us
+// against 61; 2,449,029 x 256 x 47: 0.91 ms against 0.85 here)
+constexpr int64_t kTnsMinK = 262144;
 
 struct TnsPlan {
   int nb = 0, m_tiles = 0, n_tiles = 0, wpw = 0, gy = 0;
@@ -1797,22 +1670,36 @@ void launch_tns(const TnsPlan& p, int64_t M, int64_t N, int64_t K, const float* 
 
 }  // namespace
 
+constexpr int64_t kSplitMinWork = 1500000000;  // M N K
+constexpr int64_t kSplitMinRows = 4096;
+
+gcn_status sum_partials(int64_t M, int64_t N, int64_t chunks, const float* part, float* C,
+                        int64_t ldc, hipStream_t stream) {
+  ProfScope ps("gemm_sum_partials", stream);
+  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)ceil_div(M * N, (int64_t)64)), dim3(kThreads),
+                     0, stream, M, N, chunks, part, C, ldc);
+  GCN_HIP(hipGetLastError());
+  return GCN_OK;
+}
+
 gcn_status gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                     const float* B, int64_t ldb, float* C, int64_t ldc, hipStream_t stream,
                     const float* mask, int64_t ldm, bool relu) {
   if (M == 0 || N == 0) return GCN_OK;
   const bool vec = aligned16(A, lda) && aligned16(B, ldb);
   if (op == GCN_GEMM_TN) {
-    // chunk length: kSplitRows, shrunk (down to kSplitRowsMin) when the output
-    // has few tiles so the grid still fills the chip, and grown so the chunk
-    // count fits the grid's z range
-    const int64_t tiles = ceil_div(M, (int64_t)128) * ceil_div(N, (int64_t)tile_n_narrow(N));
-    int64_t split = kSplitRows;
-    while (split > kSplitRowsMin && tiles * ceil_div(K, split) < kTnMinBlocks) split /= 2;
-    split = std::max<int64_t>(split, ceil_div(ceil_div(K, 65535), kKc) * kKc);
-    int64_t n_chunks = std::max<int64_t>(1, ceil_div(K, split));
     // small outputs (up to 16 tiles of 64 x 64) stream both operands
     const TnsPlan tp = vec ? tns_plan(M, N, K) : TnsPlan();
+    if (!tp.nb && gemm_split_tn_takes(M, N, K, lda, ldb)) {
+      GCN_CHECK(gemm_split_tn(M, N, K, A, lda, B, ldb, C, ldc, stream));
+      if (mask) GCN_CHECK(relu_bwd(M, N, mask, ldm, C, ldc, stream));
+      if (relu) GCN_CHECK(relu_fwd(M, N, C, ldc, stream));
+      return GCN_OK;
+    }
+    // chunk length: kSplitRows, grown so the chunk count fits the grid's z range
+    const int64_t split =
+        std::max<int64_t>(kSplitRows, ceil_div(ceil_div(K, (int64_t)65535), (int64_t)kKc) * kKc);
+    int64_t n_chunks = std::max<int64_t>(1, ceil_div(K, split));
     if (tp.nb) n_chunks = tp.n_chunks;
     float* part = nullptr;
     GCN_CHECK(talloc(&part, n_chunks * M * N, stream, "GEMM partials"));
@@ -1820,8 +1707,6 @@ gcn_status gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int
       ProfScope ps("gemm_tn_partial", stream);
       if (tp.nb)
         launch_tns(tp, M, N, K, A, lda, B, ldb, part, stream);
-      else if (vec)
-        launch_tn(M, N, K, split, n_chunks, A, lda, B, ldb, part, stream);
       else
         hipLaunchKernelGGL(k_gemm_tn_partial, dim3((unsigned)ceil_div(M, kTile),
                                                    (unsigned)ceil_div(N, kTile),
@@ -1833,18 +1718,21 @@ gcn_status gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int
         return hip_fail(e, "k_gemm_tn_partial", __FILE__, __LINE__);
       }
     }
-    {
-      ProfScope ps("gemm_sum_partials", stream);
-      hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)ceil_div(M * N, (int64_t)64)), dim3(kThreads),
-                         0, stream, M, N, n_chunks, (const float*)part, C, ldc);
-      hipError_t e = hipGetLastError();
-      tfree(part, stream);
-      if (e != hipSuccess) return hip_fail(e, "k_sum_partials", __FILE__, __LINE__);
-    }
+    const gcn_status st = sum_partials(M, N, n_chunks, part, C, ldc, stream);
+    tfree(part, stream);
+    GCN_CHECK(st);
     if (mask) GCN_CHECK(relu_bwd(M, N, mask, ldm, C, ldc, stream));
     if (relu) GCN_CHECK(relu_fwd(M, N, C, ldc, stream));
     return GCN_OK;
   }
+  // Three-part products on the bf16 matrix cores: outputs of more than 64
+  // columns once the product outweighs packing B (65,536 x 256 x 100: 41 us
+  // against 51; 16,384 x 256 x 100: 35 against 21), and every unaligned one
+  // that is not tiny (the general kernel loads element by element: 500,000 x
+  // 47 x 256 418 us). Narrower aligned outputs are bound by reading A either way.
+  if ((vec ? N > 64 && M * N * K >= kSplitMinWork : M >= kSplitMinRows) &&
+      gemm_split_tall_takes(M, N, K, lda, ldc, mask ? ldm : 0))
+    return gemm_split_tall(op, M, N, K, A, lda, B, ldb, C, ldc, mask, ldm, relu, stream);
   const dim3 grid((unsigned)ceil_div(M, kTile), (unsigned)ceil_div(N, kTile));
   ProfScope ps(op == GCN_GEMM_NN ? "gemm_nn" : "gemm_nt", stream);
   if (vec && op == GCN_GEMM_NN)

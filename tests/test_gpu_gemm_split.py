@@ -1,0 +1,116 @@
+"""GPU parity of the fp32 products on the bf16 matrix cores.
+
+Against float64 products of the same inputs, within 1e-5 of the sum of |terms|
+per element (a sum of K <= 4096 terms with one rounding per 16 of each of six
+part products is within 6 K / 16 * 2^-24 <= 9.2e-5 at the very worst, and
+rounding errors of either sign leave a few 1e-7), on both sides of the column,
+row and K tiles; and infinities and NaN where an fp32 product has them.
+"""
+
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import assert_close, dev, host, note
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2411_16025_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+def _pair(A, B):
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    return A64 @ B64, np.abs(A64) @ np.abs(B64)
+
+
+# contiguous operands of odd widths (every load 4-byte aligned), 1 to 9 column
+# blocks of 32, K around the 16-deep step, rows around the 64-, 128- and
+# 256-row tiles; the aligned ones are large enough to leave the general tile
+TALL = [(4096, 2, 17), (4097, 33, 16), (4223, 47, 256), (5000, 65, 31), (4096, 97, 33),
+        (4100, 161, 47), (4099, 255, 19), (4161, 257, 63), (32769, 301, 21), (33023, 256, 200),
+        (70001, 100, 256), (16448, 200, 516)]
+
+
+@pytest.mark.parametrize("M,N,K", TALL)
+def test_tall(G, M, N, K):
+    import torch
+    note("split tall %dx%dx%d" % (M, N, K))
+    A, B = synth.uniform(301, M, K), synth.uniform(302, K, N)
+    ref, S = _pair(A, B)
+    C = torch.full((M, N + 3), 7.0, device="cuda:0")
+    out = G.gcn_gemm_f32(G.GCN_GEMM_NN, dev(A), dev(B), C=C[:, :N])
+    assert_close(host(out), ref, S, what="NN")
+    assert np.all(host(C)[:, N:] == 7.0)
+    again = G.gcn_gemm_f32(G.GCN_GEMM_NN, dev(A), dev(B))
+    assert torch.equal(again.view(torch.int32), out.contiguous().view(torch.int32))
+    out = G.gcn_gemm_f32(G.GCN_GEMM_NT, dev(A), dev(np.ascontiguousarray(B.T)))
+    assert_close(host(out), ref, S, what="NT")
+
+
+# every tile width, one and several chunks, partial steps, an odd and an even
+# number of chunks (the sign alternates), both tile sizes of wide outputs
+TN = [(64, 1, 1), (255, 33, 31), (257, 129, 32), (1000, 47, 33), (4111, 128, 64), (4111, 100, 65),
+      (20000, 257, 129), (9999, 16, 300), (131073, 129, 130), (140001, 300, 257)]
+
+
+@pytest.mark.parametrize("K,M,N", TN)
+def test_tn(G, K, M, N):
+    import torch
+    note("split tn %dx%dx%d" % (K, M, N))
+    A, B = synth.uniform(303, K, M), synth.uniform(304, K, N)
+    ref, S = _pair(np.ascontiguousarray(A.T), B)
+    C = G.gcn_gemm_f32(G.GCN_GEMM_TN, dev(A), dev(B))
+    assert_close(host(C), ref, S, what="TN")
+    C2 = G.gcn_gemm_f32(G.GCN_GEMM_TN, dev(A), dev(B))
+    assert torch.equal(C.view(torch.int32), C2.view(torch.int32))
+
+
+def test_bias_cancels_over_rows(G):
+    """Column sums of a product of a million rows: a rounding of one sign in
+    every element would add up (2e-9 of an element's size, a million times)."""
+    import torch
+    note("split bias")
+    A = torch.randn(1 << 20, 128, device="cuda:0")
+    B = torch.randn(128, 128, device="cuda:0")
+    C = G.gcn_gemm_f32(G.GCN_GEMM_NN, A, B)
+    err = (C.double() - A.double() @ B.double()).sum(0)
+    # 2^20 independent errors of about 2.5e-7 * sqrt(128) each: 3e-3; six deviations
+    assert err.abs().max().item() < 6 * 1024 * 2.5e-7 * 128 ** 0.5
+
+
+@pytest.mark.parametrize("op", ["NN", "NT", "TN"])
+def test_not_finite(G, op):
+    import torch
+    note("split not finite %s" % op)
+    M, N, K = (5000, 47, 33) if op != "TN" else (40, 47, 5000)
+    A, B = synth.uniform(305, M, K), synth.uniform(306, K, N)
+    A[3, 5] = np.inf
+    A[17, 2] = np.nan
+    A[39, 7] = 3.4e38   # rounds up to infinity in bf16
+    B[7, 1] = 0.5
+    B[7, 2] = 8.0       # overflows
+    B[5, 4] = 0.0       # inf * 0
+    with np.errstate(all="ignore"):
+        ref = A.astype(np.float64) @ B.astype(np.float64)
+        want = ref.astype(np.float32)
+    if op == "TN":
+        C = G.gcn_gemm_f32(G.GCN_GEMM_TN, dev(np.ascontiguousarray(A.T)), dev(B))
+    elif op == "NT":
+        C = G.gcn_gemm_f32(G.GCN_GEMM_NT, dev(A), dev(np.ascontiguousarray(B.T)))
+    else:
+        C = G.gcn_gemm_f32(G.GCN_GEMM_NN, dev(A), dev(B))
+    got = host(C)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(np.isinf(got), np.isinf(want))
+    inf = np.isinf(want)
+    assert np.array_equal(got[inf], want[inf])
+    fin = np.isfinite(want)
+    scale = np.nan_to_num(np.abs(A), nan=0, posinf=0).astype(np.float64) @ np.abs(B).astype(np.float64)
+    assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-5 * scale[fin])
