@@ -31,10 +31,10 @@
  *    untouched.
  *  - Calls that share a gcn_graph may run concurrently only if none of them
  *    is gcn_normalize or gcn_graph_free.
- *  - Temporaries are allocated stream-ordered from the device's default
- *    memory pool; on first use the library sets that pool's release
- *    threshold to keep freed blocks for reuse (they stay reserved for the
- *    process).
+ *  - Temporaries are allocated stream-ordered and kept, per stream, for the
+ *    next call on it: at most a quarter of the device's memory is kept idle.
+ *    It is given back when an allocation of the library fails, and all but
+ *    256 MiB of it when the last graph on the device is freed.
  */
 #ifndef GCNAGG_H
 #define GCNAGG_H

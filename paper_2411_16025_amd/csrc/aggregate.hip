@@ -886,6 +886,7 @@ using namespace gcn;
 extern "C" gcn_status gcn_aggregate_fwd(const gcn_graph* g, const void* X, int64_t ldx, int dtype,
                                         float* Y, int64_t ldy, int64_t F, void* stream) {
   clear_error();
+  CallScope scope(stream);
   GCN_CHECK(check_common(g, F));
   return aggregate(g->csr, X, ldx, dtype, Y, ldy, F, stream);
 }
@@ -893,6 +894,7 @@ extern "C" gcn_status gcn_aggregate_fwd(const gcn_graph* g, const void* X, int64
 extern "C" gcn_status gcn_aggregate_bwd(const gcn_graph* g, const void* G, int64_t ldg, int dtype,
                                         float* dX, int64_t lddx, int64_t F, void* stream) {
   clear_error();
+  CallScope scope(stream);
   GCN_CHECK(check_common(g, F));
   return aggregate(g->csc, G, ldg, dtype, dX, lddx, F, stream);
 }
@@ -904,6 +906,7 @@ extern "C" gcn_status gcn_aggregate_fwd_q8halo(const gcn_graph* g, int64_t n_loc
                                                int64_t ldp, float* Y, int64_t ldy, int64_t F,
                                                uint32_t flags, void* stream) {
   clear_error();
+  CallScope scope(stream);
   GCN_CHECK(check_common(g, F));
   if (flags & ~(uint32_t)(GCN_Q8_USE_CSC | GCN_Q_CODES_2BIT)) {
     set_error("unknown q8halo flag bits 0x%x", flags);
@@ -998,6 +1001,7 @@ extern "C" gcn_status gcn_aggregate_fwd_noalloc(const gcn_graph* g, const void* 
                                                 int dtype, float* Y, int64_t ldy, int64_t F,
                                                 void* stream) {
   clear_error();
+  CallScope scope(stream);
   GCN_CHECK(check_common(g, F));
   GCN_CHECK(check_plain(X, ldx, dtype, Y, ldy, F));
   const int64_t need = parts_floats(g->csr, F);

@@ -474,6 +474,15 @@ int64_t env_int(const char* name, int64_t dflt, int64_t lo, int64_t hi) {
   return (v < lo || v > hi) ? dflt : (int64_t)v;
 }
 
+// the entries and the row pointers of a matrix whose nnz is known
+gcn_status alloc_arrays(Mat& m) {
+  Slab slab;
+  slab.add(&m.ent, m.nnz);
+  slab.add(&m.ptr, m.n_major + 1);
+  void* base = nullptr;
+  return slab.alloc(&base, "entries and row pointers");  // base == m.ent
+}
+
 // Sorted CSR from already-generated keys (sentinel-padded). Takes ownership
 // of nothing; `major` receives the row id of every stored entry.
 gcn_status keys_to_csr(uint64_t** keys, uint64_t** alt, int64_t m, int keybits, int colbits,
@@ -488,17 +497,13 @@ gcn_status keys_to_csr(uint64_t** keys, uint64_t** alt, int64_t m, int keybits, 
   tfree(scratch, stream);
   GCN_CHECK(st);
   // one host synchronization: entry count and the id-range flag
-  int64_t* pinned = nullptr;
-  GCN_HIP(hipHostMalloc((void**)&pinned, 2 * sizeof(int64_t), hipHostMallocDefault));
-  pinned[0] = pinned[1] = 0;
-  hipError_t e1 = hipMemcpyAsync(&pinned[0], pos + m, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
-  hipError_t e2 = err_dev ? hipMemcpyAsync(&pinned[1], err_dev, sizeof(int), hipMemcpyDeviceToHost,
+  int64_t nnz = 0;
+  int errv = 0;
+  hipError_t e1 = hipMemcpyAsync(&nnz, pos + m, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
+  hipError_t e2 = err_dev ? hipMemcpyAsync(&errv, err_dev, sizeof(int), hipMemcpyDeviceToHost,
                                            stream)
                           : hipSuccess;
   hipError_t e3 = hipStreamSynchronize(stream);
-  const int64_t nnz = pinned[0];
-  const int errv = (int)pinned[1];
-  (void)hipHostFree(pinned);
   if (e1 != hipSuccess) return hip_fail(e1, "hipMemcpyAsync(nnz)", __FILE__, __LINE__);
   if (e2 != hipSuccess) return hip_fail(e2, "hipMemcpyAsync(err)", __FILE__, __LINE__);
   if (e3 != hipSuccess) return hip_fail(e3, "hipStreamSynchronize", __FILE__, __LINE__);
@@ -506,8 +511,7 @@ gcn_status keys_to_csr(uint64_t** keys, uint64_t** alt, int64_t m, int keybits, 
   *nnz_host = nnz;
   if (errv) return GCN_OK;  // caller reports the range error
   mat.nnz = nnz;
-  GCN_CHECK(dalloc(&mat.ent, nnz, "entries"));
-  GCN_CHECK(dalloc(&mat.ptr, mat.n_major + 1, "row pointers"));
+  GCN_CHECK(alloc_arrays(mat));
   GCN_CHECK(talloc(major, nnz, stream, "entry rows"));
   if (m > 0) {
     hipLaunchKernelGGL(k_compact, dim3(grid_for(m)), dim3(kThreads), 0, stream, *keys,
@@ -530,8 +534,7 @@ gcn_status transpose_csr(const Mat& a, const int32_t* a_major, Mat& t, hipStream
   int32_t* major = nullptr;
   gcn_status st = talloc(&keys, nnz, stream, "transpose keys");
   if (st == GCN_OK) st = talloc(&alt, nnz, stream, "transpose keys");
-  if (st == GCN_OK) st = dalloc(&t.ent, nnz, "transpose entries");
-  if (st == GCN_OK) st = dalloc(&t.ptr, t.n_major + 1, "transpose row pointers");
+  if (st == GCN_OK) st = alloc_arrays(t);
   if (st == GCN_OK) st = talloc(&major, nnz, stream, "transpose rows");
   if (st == GCN_OK && nnz > 0) {
     hipLaunchKernelGGL(k_transpose_keys, dim3(grid_for(nnz)), dim3(kThreads), 0, stream, a.ent,
@@ -585,7 +588,13 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
   GCN_CHECK(tmp.alloc(&keys, n, "class keys"));
   GCN_CHECK(tmp.alloc(&sorted, n, "class keys"));
   GCN_CHECK(tmp.alloc(&counts, 2 * kNumClasses, "class counts"));
-  GCN_CHECK(dalloc(&p.rows, n, "class rows"));
+  {
+    Slab slab;
+    slab.add(&p.rows, n);
+    slab.add(&p.rbeg, n);
+    slab.add(&p.rlen, n);
+    GCN_CHECK(slab.alloc(&p.slab, "class rows"));
+  }
   GCN_HIP(hipMemsetAsync(counts, 0, 2 * kNumClasses * sizeof(unsigned long long), stream));
   hipLaunchKernelGGL(k_class_keys, dim3(grid_for(n)), dim3(kThreads), 0, stream, m.ptr, n,
                      p.medium_max, keys);
@@ -613,8 +622,6 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
   // load fewer in their chain of dependent loads)
   const int64_t n_rowk = p.class_off[kMedium + 1] - p.class_off[kFirstShort];
   if (n_rowk > 0) {
-    GCN_CHECK(dalloc(&p.rbeg, n_rowk, "row starts"));
-    GCN_CHECK(dalloc(&p.rlen, n_rowk, "row lengths"));
     hipLaunchKernelGGL(k_row_begins, dim3(grid_for(n_rowk)), dim3(kThreads), 0, stream,
                        (const int32_t*)(p.rows + p.class_off[kFirstShort]), n_rowk,
                        (const int64_t*)m.ptr, p.rbeg, p.rlen);
@@ -687,13 +694,24 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
     set_error("too many partial rows (%lld)", (long long)p.n_parts);
     return GCN_ERANGE;
   }
-  GCN_CHECK(dalloc(&p.giant_row, p.n_giant, "giant rows"));
-  GCN_CHECK(dalloc(&p.giant_part_off, p.n_giant + 1, "giant partial offsets"));
+  {
+    Slab slab;
+    slab.add(&p.giant_row, p.n_giant);
+    slab.add(&p.giant_part_off, p.n_giant + 1);
+    if (nch > 0) {
+      slab.add(&p.chunk_row, p.n_chunks);
+      slab.add(&p.chunk_beg, p.n_chunks);
+      slab.add(&p.chunk_end, p.n_chunks);
+      slab.add(&p.chunk_part, p.n_chunks);
+    }
+    if (nb > 0) {
+      slab.add(&p.piece_beg, p.n_pieces);
+      slab.add(&p.piece_len, p.n_pieces);
+      slab.add(&p.piece_part, p.n_pieces);
+    }
+    GCN_CHECK(slab.alloc(&p.cut_slab, "chunk and piece tables"));
+  }
   if (nch > 0) {
-    GCN_CHECK(dalloc(&p.chunk_row, p.n_chunks, "chunk rows"));
-    GCN_CHECK(dalloc(&p.chunk_beg, p.n_chunks, "chunk starts"));
-    GCN_CHECK(dalloc(&p.chunk_end, p.n_chunks, "chunk ends"));
-    GCN_CHECK(dalloc(&p.chunk_part, p.n_chunks, "chunk partial slots"));
     hipLaunchKernelGGL(k_chunks, dim3(grid_for(nch)), dim3(kThreads), 0, stream, chrow, nch,
                        m.ptr, p.chunk_len, (const int64_t*)chunk_off, (const int64_t*)part_off,
                        (const int64_t*)giant_idx, p.chunk_row, p.chunk_beg, p.chunk_end,
@@ -718,9 +736,6 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
     GCN_CHECK(radix_pass_u64(keys, alt, p.n_pieces, 32, stream));
     GCN_CHECK(radix_pass_u64(alt, keys, p.n_pieces, 40, stream));
     GCN_CHECK(radix_pass_u64(keys, alt, p.n_pieces, 48, stream));
-    GCN_CHECK(dalloc(&p.piece_beg, p.n_pieces, "piece starts"));
-    GCN_CHECK(dalloc(&p.piece_len, p.n_pieces, "piece lengths"));
-    GCN_CHECK(dalloc(&p.piece_part, p.n_pieces, "piece partial slots"));
     hipLaunchKernelGGL(k_order_pieces, dim3(grid_for(p.n_pieces)), dim3(kThreads), 0, stream,
                        (const uint64_t*)alt, p.n_pieces, (const int64_t*)tbeg,
                        (const int32_t*)tlen, n_cparts, p.piece_beg, p.piece_len, p.piece_part);
@@ -731,23 +746,10 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
 
 void free_mat(Mat& m, bool arrays) {
   Plan& p = m.plan;
-  dfree(p.rows);
-  dfree(p.rbeg);
-  dfree(p.rlen);
-  dfree(p.chunk_row);
-  dfree(p.chunk_beg);
-  dfree(p.chunk_end);
-  dfree(p.chunk_part);
-  dfree(p.giant_row);
-  dfree(p.giant_part_off);
-  dfree(p.piece_beg);
-  dfree(p.piece_len);
-  dfree(p.piece_part);
+  dfree(p.slab);
+  dfree(p.cut_slab);
   p = Plan();
-  if (arrays) {
-    dfree(m.ptr);
-    dfree(m.ent);
-  }
+  if (arrays) dfree(m.ent);  // and with it the row pointers
   m.ptr = nullptr;
   m.ent = nullptr;
 }
@@ -760,11 +762,13 @@ namespace {
 
 void destroy(gcn_graph* g) {
   if (!g) return;
+  const int dev = g->device;
   if (!g->csc_shared) free_mat(g->csc, true);
   if (g->csc_shared && g->csc_own_ent) dfree(g->csc.ent);
   free_mat(g->csr, true);
   g->magic = kFreed;
   delete g;
+  graph_closed(dev);
 }
 
 gcn_status build_impl(int64_t n_rows, int64_t n_cols, int64_t n_edges, const int32_t* src,
@@ -844,6 +848,7 @@ extern "C" gcn_status gcn_build_csr(int64_t n_rows, int64_t n_cols, int64_t n_ed
                                     const int32_t* src, const int32_t* dst, uint32_t flags,
                                     void* stream, gcn_graph** out) {
   clear_error();
+  CallScope scope(stream);
   if (!out) {
     set_error("out is NULL");
     return GCN_EINVAL;
@@ -887,6 +892,7 @@ extern "C" gcn_status gcn_build_csr(int64_t n_rows, int64_t n_cols, int64_t n_ed
   }
   g->magic = kMagic;
   g->device = dev;
+  graph_opened(dev);
   g->n_rows = n_rows;
   g->n_cols = n_cols;
   g->flags = flags;
@@ -992,6 +998,7 @@ gcn_status normalize_with(gcn_graph* g, const int32_t* deg_rows, const int32_t* 
 
 extern "C" gcn_status gcn_normalize(gcn_graph* g, const int32_t* deg, void* stream_) {
   clear_error();
+  CallScope scope(stream_);
   GCN_CHECK(check_graph(g));
   hipStream_t stream = (hipStream_t)stream_;
   if (!deg && g->n_rows != g->n_cols) {
@@ -1015,6 +1022,7 @@ extern "C" gcn_status gcn_normalize(gcn_graph* g, const int32_t* deg, void* stre
 
 extern "C" gcn_status gcn_normalize_mean(gcn_graph* g, void* stream_) {
   clear_error();
+  CallScope scope(stream_);
   GCN_CHECK(check_graph(g));
   hipStream_t stream = (hipStream_t)stream_;
   // the transpose keeps the shared structure but needs values of its own
@@ -1036,6 +1044,7 @@ extern "C" gcn_status gcn_normalize_mean(gcn_graph* g, void* stream_) {
 extern "C" gcn_status gcn_normalize_rc(gcn_graph* g, const int32_t* deg_rows,
                                        const int32_t* deg_cols, void* stream_) {
   clear_error();
+  CallScope scope(stream_);
   GCN_CHECK(check_graph(g));
   hipStream_t stream = (hipStream_t)stream_;
   if (!deg_rows || !deg_cols) {
@@ -1050,6 +1059,7 @@ extern "C" gcn_status gcn_normalize_rc(gcn_graph* g, const int32_t* deg_rows,
 extern "C" gcn_status gcn_graph_export(const gcn_graph* g, int which, int64_t* ptr, int32_t* idx,
                                        float* val, void* stream_) {
   clear_error();
+  CallScope scope(stream_);
   GCN_CHECK(check_graph(g));
   if (which != 0 && which != 1) {
     set_error("which must be 0 (A) or 1 (A^T)");
@@ -1081,6 +1091,7 @@ extern "C" gcn_status gcn_graph_export(const gcn_graph* g, int which, int64_t* p
 extern "C" gcn_status gcn_graph_bins(const gcn_graph* g, int which, int64_t halo_from,
                                      int64_t* records, int cap, int* n_classes, void* stream_) {
   clear_error();
+  CallScope scope(stream_);
   GCN_CHECK(check_graph(g));
   if (which != 0 && which != 1) {
     set_error("which must be 0 (A) or 1 (A^T)");

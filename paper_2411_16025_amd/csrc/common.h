@@ -36,6 +36,8 @@ constexpr int kMedium = 7;
 constexpr int kChunked = 8;
 
 struct Plan {
+  void* slab = nullptr;      // the one allocation that holds rows, rbeg and rlen
+  void* cut_slab = nullptr;  // ... and the one of the chunk, piece and giant-row tables
   int32_t* rows = nullptr;        // [n_major] row ids grouped by class (order: see build_plan)
   // first entry and length of each row of the classes 1 .. kMedium, in the
   // order of `rows` from class_off[1] (the row kernels read them with the
@@ -79,7 +81,7 @@ struct Plan {
 
 struct Mat {
   int64_t n_major = 0, n_minor = 0, nnz = 0;
-  int64_t* ptr = nullptr;  // [n_major + 1]
+  int64_t* ptr = nullptr;  // [n_major + 1], after the entries in the same allocation
   Ent* ent = nullptr;      // [nnz]
   Plan plan;
 };
@@ -124,7 +126,29 @@ gcn_status dalloc(T** p, int64_t count, const char* what) {
   return dmalloc(reinterpret_cast<void**>(p), (size_t)(count > 0 ? count : 1) * sizeof(T), what);
 }
 void dfree(void* p);
-// Stream-ordered temporaries (hipMallocAsync / hipFreeAsync on `stream`).
+// Several arrays in one allocation (hipMalloc and hipFree cost about 60 and
+// 150 us each): add() the arrays, then alloc() sets their pointers.
+struct Slab {
+  struct Part {
+    void** p;
+    size_t off;
+  };
+  Part parts[16];
+  int n = 0;
+  size_t bytes = 0;
+  template <class T>
+  void add(T** p, int64_t count) {
+    parts[n++] = {reinterpret_cast<void**>(p), bytes};
+    bytes += ((size_t)(count > 0 ? count : 1) * sizeof(T) + 255) & ~size_t(255);
+  }
+  gcn_status alloc(void** base, const char* what) {
+    GCN_CHECK(dmalloc(base, bytes, what));
+    for (int i = 0; i < n; ++i) *parts[i].p = static_cast<char*>(*base) + parts[i].off;
+    return GCN_OK;
+  }
+};
+// Temporaries of the work enqueued on `stream`, kept for later calls on it
+// (runtime.hip).
 gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what);
 template <class T>
 gcn_status talloc(T** p, int64_t count, hipStream_t stream, const char* what) {
@@ -132,6 +156,21 @@ gcn_status talloc(T** p, int64_t count, hipStream_t stream, const char* what) {
                  what);
 }
 void tfree(void* p, hipStream_t stream);
+// One per entry point that takes temporaries, from its start to its end (see
+// runtime.hip); calls without one are ordered block by block.
+struct CallScope {
+  hipStream_t stream;
+  CallScope* outer;
+  int dev = 0;
+  bool waited = false, released = false;
+  explicit CallScope(void* stream);
+  CallScope(const CallScope&) = delete;
+  CallScope& operator=(const CallScope&) = delete;
+  ~CallScope();
+};
+// Graphs alive per device (idle temporaries are given back with the last one).
+void graph_opened(int dev);
+void graph_closed(int dev);
 
 // Work that may overlap the caller's stream runs on a second stream of the
 // current device (non-blocking, default priority, created on first use and

@@ -1991,6 +1991,7 @@ extern "C" gcn_status gcn_gemm_f32(int op, int64_t M, int64_t N, int64_t K, cons
                                    int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
                                    void* stream) {
   clear_error();
+  CallScope scope(stream);
   if (op != GCN_GEMM_NN && op != GCN_GEMM_NT && op != GCN_GEMM_TN) {
     set_error("unknown GEMM op %d", op);
     return GCN_EINVAL;
@@ -2035,6 +2036,7 @@ extern "C" gcn_status gcn_softmax_xent(int64_t n, int64_t C, const float* logits
                                        const int32_t* labels, float* dlogits, int64_t ldd,
                                        double* loss, void* stream) {
   clear_error();
+  CallScope scope(stream);
   if (n <= 0 || C <= 0 || C > 64 || !logits || !labels || !dlogits || !loss || ld < C ||
       ldd < C) {
     set_error("invalid softmax cross-entropy arguments (1 <= C <= 64)");

@@ -669,6 +669,7 @@ extern "C" gcn_status gcn_sage3_forward(const gcn_graph* g, const float* X, int6
                                         float* H1, int64_t ldh1, float* H2, int64_t ldh2,
                                         float* logits, int64_t ldl, void* stream_) {
   clear_error();
+  CallScope scope(stream_);
   GCN_CHECK(check_args(g, X, ldx, f_in, hidden, n_classes, params, labels, lp_mask, E, eps));
   if ((H1 && ldh1 < hidden) || (H2 && ldh2 < hidden) || (logits && ldl < n_classes)) {
     set_error("output leading dimensions must cover the output widths");
@@ -692,6 +693,7 @@ extern "C" gcn_status gcn_sage3_step(const gcn_graph* g, const float* X, int64_t
                                      float* const* grads, float* dE, double* loss,
                                      void* stream_) {
   clear_error();
+  CallScope scope(stream_);
   GCN_CHECK(check_args(g, X, ldx, f_in, hidden, n_classes, params, labels, lp_mask, E, eps));
   if (!grads || !labels || !loss || (lp_mask && !dE)) {
     set_error("the step needs labels, grads, loss (and dE with label propagation)");

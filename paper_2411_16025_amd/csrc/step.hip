@@ -26,6 +26,7 @@ extern "C" gcn_status gcn_gcn2_step(const gcn_graph* g, const float* X, int64_t 
                                     int64_t n_classes, const int32_t* labels, float* dW1,
                                     float* dW2, double* loss, void* stream_) {
   clear_error();
+  CallScope scope(stream_);
   GCN_CHECK(check_graph(g));
   if (g->n_rows != g->n_cols) {
     set_error("the GCN step needs a square graph");
