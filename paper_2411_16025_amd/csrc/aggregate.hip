@@ -50,8 +50,9 @@ namespace gcn {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef uint16_t us4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t us4u __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u1u __attribute__((aligned(1)));
 
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
@@ -62,13 +63,17 @@ constexpr int kWavesPerBlock = kBlock / 64;
 // [f0, f0 + VEC) of input row j into raw registers) and decode (turn the raw
 // registers into fp32 values). A loop issues the fetches of a whole group of
 // entries before it decodes any of them, so no load waits on the arithmetic
-// of another. TAIL = false promises F % VEC == 0: every fetch is then one
-// unguarded vector load, and clamp() moves a lane's f0 past the row end back
-// into the row, so a loop may fetch on every lane and discard the values of
-// lanes or entries it does not use (no divergent branches around the loads).
-// TAIL = true guards each feature against F instead.
+// of another. Every fetch is one unguarded load of VEC features: clamp() moves
+// a lane whose features reach past the row's end back to its last VEC
+// features. For F % VEC != 0 the row's last lane then repeats features of the
+// lane before it (and stores the same sums to the same place), and lanes or
+// entries that are not used are discarded, so there are no divergent branches
+// around the loads. Rows need no alignment beyond their element's: the loads
+// and stores are of unaligned vector types (one 16-byte instruction all the
+// same; 47 contiguous features, 2.45M nodes: 3.65 ms a pass with a 4-byte load
+// per lane, 2.7 with these).
 
-template <int VEC, bool TAIL>
+template <int VEC>
 struct SrcF32 {
   const float* __restrict__ x;
   uint32_t ld;  // row strides fit 32 bits (checked on the host): one 32 x 32 -> 64-bit multiply
@@ -76,17 +81,12 @@ struct SrcF32 {
   struct Raw {
     float v[VEC];
   };
-  __device__ inline int clamp(int f0) const { return TAIL || f0 <= F - VEC ? f0 : F - VEC; }
+  __device__ inline int clamp(int f0) const { return f0 <= F - VEC ? f0 : F - VEC; }
   __device__ inline void fetch(int32_t j, int f0, Raw& r) const {
     const float* p = x + (uint64_t)(uint32_t)j * ld + f0;
     if constexpr (VEC == 4) {
-      if (!TAIL || f0 + 4 <= F) {
-        const f4 v = *reinterpret_cast<const f4*>(p);
-        r.v[0] = v.x; r.v[1] = v.y; r.v[2] = v.z; r.v[3] = v.w;
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) r.v[v] = (f0 + v < F) ? p[v] : 0.f;
-      }
+      const f4u v = *reinterpret_cast<const f4u*>(p);
+      r.v[0] = v.x; r.v[1] = v.y; r.v[2] = v.z; r.v[3] = v.w;
     } else {
       r.v[0] = p[0];
     }
@@ -99,7 +99,7 @@ struct SrcF32 {
 
 __device__ inline float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-template <int VEC, bool TAIL>
+template <int VEC>
 struct SrcBF16 {
   const uint16_t* __restrict__ x;
   uint32_t ld;
@@ -107,17 +107,12 @@ struct SrcBF16 {
   struct Raw {
     uint16_t v[VEC];
   };
-  __device__ inline int clamp(int f0) const { return TAIL || f0 <= F - VEC ? f0 : F - VEC; }
+  __device__ inline int clamp(int f0) const { return f0 <= F - VEC ? f0 : F - VEC; }
   __device__ inline void fetch(int32_t j, int f0, Raw& r) const {
     const uint16_t* p = x + (uint64_t)(uint32_t)j * ld + f0;
     if constexpr (VEC == 4) {
-      if (!TAIL || f0 + 4 <= F) {
-        const us4 v = *reinterpret_cast<const us4*>(p);
-        r.v[0] = v.x; r.v[1] = v.y; r.v[2] = v.z; r.v[3] = v.w;
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) r.v[v] = (f0 + v < F) ? p[v] : (uint16_t)0;
-      }
+      const us4u v = *reinterpret_cast<const us4u*>(p);
+      r.v[0] = v.x; r.v[1] = v.y; r.v[2] = v.z; r.v[3] = v.w;
     } else {
       r.v[0] = p[0];
     }
@@ -133,7 +128,7 @@ struct SrcBF16 {
 // scale: x = fmaf(q, S, Z), exactly one rounding. A halo row's raw registers
 // hold the packed codes, Z and S in the slots a local row uses for its
 // features, so both kinds cost the same registers (separate registers cost
-// occupancy and time).
+// occupancy and time). TAIL: 2-bit codes of F % 4 != 0 features.
 template <int VEC, int BITS, bool TAIL>
 struct SrcQ {
   const float* __restrict__ x;
@@ -148,11 +143,11 @@ struct SrcQ {
   struct Raw {
     float v[VEC < 3 ? 3 : VEC];  // local: features; halo: {codes, Z, S}
   };
-  __device__ inline int clamp(int f0) const { return TAIL || f0 <= F - VEC ? f0 : F - VEC; }
+  __device__ inline int clamp(int f0) const { return f0 <= F - VEC ? f0 : F - VEC; }
   __device__ inline void fetch(int32_t j, int f0, Raw& r) const {
     if ((uint32_t)j < n_local) {
-      typename SrcF32<VEC, TAIL>::Raw fr;
-      SrcF32<VEC, TAIL>{x, ldx, F}.fetch(j, f0, fr);
+      typename SrcF32<VEC>::Raw fr;
+      SrcF32<VEC>{x, ldx, F}.fetch(j, f0, fr);
 #pragma unroll
       for (int v = 0; v < VEC; ++v) r.v[v] = fr.v[v];
       return;
@@ -165,18 +160,17 @@ struct SrcQ {
     r.v[2] = scale[po];
     uint32_t c;
     if constexpr (BITS == 2) {
-      // byte f0 / 4 holds the codes of features f0 .. f0 + 3 (VEC = 4: f0 % 4 == 0)
+      // byte f0 / 4 holds the codes of features f0 .. f0 + 3 where f0 % 4 == 0;
+      // the last lane of a row of F % 4 != 0 features (TAIL) finds its four in two
       const uint32_t byte = qrow[f0 >> 2];
-      c = VEC == 4 ? byte : (byte >> (2 * (f0 & 3))) & 3u;
+      if constexpr (VEC == 1)
+        c = (byte >> (2 * (f0 & 3))) & 3u;
+      else if constexpr (TAIL)
+        c = (byte | (uint32_t)qrow[(f0 + 3) >> 2] << 8) >> (2 * (f0 & 3));
+      else
+        c = byte;
     } else if constexpr (VEC == 4) {
-      if (!TAIL || f0 + 4 <= F) {
-        c = *reinterpret_cast<const uint32_t*>(p);
-      } else {
-        c = 0;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (f0 + v < F) c |= (uint32_t)p[v] << (8 * v);
-      }
+      c = *reinterpret_cast<const u1u*>(p);
     } else {
       c = p[0];
     }
@@ -197,32 +191,33 @@ struct SrcQ {
   }
 };
 
-template <int VEC, bool TAIL>
-using SrcQ8 = SrcQ<VEC, 8, TAIL>;
-template <int VEC, bool TAIL>
-using SrcQ2 = SrcQ<VEC, 2, TAIL>;
+template <int VEC>
+using SrcQ8 = SrcQ<VEC, 8, false>;
+template <int VEC>
+using SrcQ2 = SrcQ<VEC, 2, false>;
+template <int VEC>
+using SrcQ2Tail = SrcQ<VEC, 2, true>;
 
 // ---- helpers -------------------------------------------------------------------
 
-// Store a finished output row tile; relu clamps it at 0 (the activation of a
-// layer fused into the aggregation that produces it).
+// Store VEC finished features at y + f (f from Src::clamp); relu clamps them
+// at 0 (the activation of a layer fused into the aggregation that produces it).
 template <int VEC, bool RELU = false>
-__device__ inline void store_row(float* __restrict__ y, int f0, int F, const float* acc_in) {
+__device__ inline void store_row(float* __restrict__ y, int f, const float* acc_in) {
   float acc[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = RELU ? fmaxf(acc_in[v], 0.f) : acc_in[v];
   if constexpr (VEC == 4) {
-    if (f0 + 4 <= F) {
-      f4 v = {acc[0], acc[1], acc[2], acc[3]};
-      __builtin_nontemporal_store(v, reinterpret_cast<f4*>(y + f0));
-    } else {
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (f0 + v < F) __builtin_nontemporal_store(acc[v], y + f0 + v);
-    }
+    f4u v = {acc[0], acc[1], acc[2], acc[3]};
+    __builtin_nontemporal_store(v, reinterpret_cast<f4u*>(y + f));
   } else {
-    __builtin_nontemporal_store(acc[0], y + f0);
+    __builtin_nontemporal_store(acc[0], y + f);
   }
+}
+
+template <int VEC>
+__device__ inline int clamp_features(int f0, int F) {
+  return f0 <= F - VEC ? f0 : F - VEC;
 }
 
 // Gathers in flight per lane in the entry loops.
@@ -415,7 +410,7 @@ __global__ __launch_bounds__(kBlock) void k_zero_rows(const int32_t* __restrict_
   float z[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) z[v] = 0.f;
-  store_row<VEC>(y + (int64_t)rows[i] * ldy, f0, F, z);
+  store_row<VEC>(y + (int64_t)rows[i] * ldy, clamp_features<VEC>(f0, F), z);
 }
 
 // Rows with exactly L entries (L = 1 or 2): one row per slot and R groups of
@@ -474,7 +469,7 @@ __global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_tiny(const int64_t* _
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[v] = __builtin_fmaf(e[g][k].val, xv[v], acc[v]);
     }
-    store_row<VEC, RELU>(y + (int64_t)r[g] * ldy, f0, F, acc);
+    store_row<VEC, RELU>(y + (int64_t)r[g] * ldy, fs, acc);
   }
 }
 
@@ -512,7 +507,7 @@ __global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_short(const int64_t* 
   }
   float acc[VEC];
   accumulate_slot<VEC, G, GCN_SLOT_UNROLL>(ent, b, len, src, f0, active, acc);
-  if (active) store_row<VEC, RELU>(y + (int64_t)r * ldy, f0, F, acc);
+  if (active) store_row<VEC, RELU>(y + (int64_t)r * ldy, src.clamp(f0), acc);
 }
 
 // One workgroup per chunk of a long row. Wavefront w of the workgroup takes
@@ -557,9 +552,9 @@ __global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_chunk(const Ent* __re
     }
     const int32_t part = chunk_part[c];
     if (part < 0)
-      store_row<VEC, RELU>(y + (int64_t)r * ldy, f0, F, acc);
+      store_row<VEC, RELU>(y + (int64_t)r * ldy, src.clamp(f0), acc);
     else
-      store_row<VEC>(parts + (int64_t)part * ldp, f0, F, acc);
+      store_row<VEC>(parts + (int64_t)part * ldp, src.clamp(f0), acc);
   }
 }
 
@@ -584,22 +579,17 @@ void k_pieces(const int64_t* __restrict__ pbeg, const int32_t* __restrict__ plen
   const int len = has ? plen[i] : 0;
   float acc[VEC];
   accumulate_slot<VEC, G, GCN_PIECE_UNROLL>(ent, b, len, src, f0, active, acc);
-  if (active) store_row<VEC>(parts + (int64_t)ppart[i] * ldp, f0, F, acc);
+  if (active) store_row<VEC>(parts + (int64_t)ppart[i] * ldp, src.clamp(f0), acc);
 }
 
-// Features f0 .. f0 + VEC - 1 of a partial row (zeros past F).
+// Features f .. f + VEC - 1 of a partial row.
 template <int VEC>
-__device__ inline void load_part(const float* __restrict__ row, int f0, int F, float* out) {
+__device__ inline void load_part(const float* __restrict__ row, int f, float* out) {
   if constexpr (VEC == 4) {
-    if (f0 + 4 <= F) {
-      const f4 v4 = *reinterpret_cast<const f4*>(row + f0);
-      out[0] = v4.x; out[1] = v4.y; out[2] = v4.z; out[3] = v4.w;
-    } else {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) out[v] = f0 + v < F ? row[f0 + v] : 0.f;
-    }
+    const f4u v4 = *reinterpret_cast<const f4u*>(row + f);
+    out[0] = v4.x; out[1] = v4.y; out[2] = v4.z; out[3] = v4.w;
   } else {
-    out[0] = row[f0];
+    out[0] = row[f];
   }
 }
 
@@ -619,6 +609,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_parts(const int32_t* __restri
   const int slot = lane / G;
   const int f0 = (int)blockIdx.y * G * VEC + (lane % G) * VEC;
   const bool active = f0 < F;
+  const int fs = clamp_features<VEC>(f0, F);
   float acc[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
@@ -631,7 +622,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_parts(const int32_t* __restri
     for (; p + (U - 1) * E < pe; p += U * E) {
       float v[U][VEC];
 #pragma unroll
-      for (int u = 0; u < U; ++u) load_part<VEC>(parts + (p + u * E) * ldp, f0, F, v[u]);
+      for (int u = 0; u < U; ++u) load_part<VEC>(parts + (p + u * E) * ldp, fs, v[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -639,13 +630,13 @@ __global__ __launch_bounds__(kBlock) void k_reduce_parts(const int32_t* __restri
     }
     for (; p < pe; p += E) {
       float v[VEC];
-      load_part<VEC>(parts + p * ldp, f0, F, v);
+      load_part<VEC>(parts + p * ldp, fs, v);
 #pragma unroll
       for (int k = 0; k < VEC; ++k) acc[k] += v[k];
     }
   }
   reduce_slots<VEC, G>(acc);
-  if (slot == 0 && active) store_row<VEC, RELU>(y + (int64_t)giant_row[i] * ldy, f0, F, acc);
+  if (slot == 0 && active) store_row<VEC, RELU>(y + (int64_t)giant_row[i] * ldy, fs, acc);
 }
 
 // ---- launch ------------------------------------------------------------------------
@@ -768,10 +759,8 @@ int64_t parts_floats(const Mat& m, int64_t F) { return m.plan.n_parts * ((F + 3)
 // Lanes per slot: smallest power of two covering min(F, 128) features with
 // 4-float lanes (at least 4 lanes); wider rows run as 128-feature tiles
 // (blockIdx.y), which beats one slot of 64 lanes per wavefront (F = 256:
-// 5% on the product-shaped graph, 16 lanes for F = 128 lose 9%); the scalar
-// path always uses 64 lanes.
-int lanes_for(int F, bool vec4) {
-  if (!vec4) return 64;
+// 5% on the product-shaped graph, 16 lanes for F = 128 lose 9%).
+int lanes_for(int F) {
   const int need = (std::min(F, 128) + 3) / 4;
   int g = 4;
   while (g < need) g <<= 1;
@@ -781,7 +770,7 @@ int lanes_for(int F, bool vec4) {
 template <class Src, bool RELU>
 gcn_status launch_vec4(const Mat& m, const Src& src, float* y, int64_t ldy, int F,
                        hipStream_t stream, float* ws) {
-  switch (lanes_for(F, true)) {
+  switch (lanes_for(F)) {
     case 4: return launch_all<4, 4, RELU>(m, src, y, ldy, F, stream, ws);
     case 8: return launch_all<4, 8, RELU>(m, src, y, ldy, F, stream, ws);
     case 16: return launch_all<4, 16, RELU>(m, src, y, ldy, F, stream, ws);
@@ -789,21 +778,13 @@ gcn_status launch_vec4(const Mat& m, const Src& src, float* y, int64_t ldy, int 
   }
 }
 
-// pad_ok: every input row may be read up to a multiple of 4 features (its
-// stride leaves room), so an odd F still takes the unguarded 16-byte loads;
-// the extra features are never stored.
-template <template <int, bool> class SrcT, bool RELU = false, class Make>
-gcn_status dispatch(const Mat& m, bool vec4, int F, float* y, int64_t ldy, hipStream_t stream,
-                    Make make, bool pad_ok = false, float* ws = nullptr) {
-  if (!vec4) return launch_all<1, 64, RELU>(m, make(SrcT<1, false>{}), y, ldy, F, stream, ws);
-  if (F % 4 != 0 && !pad_ok)
-    return launch_vec4<SrcT<4, true>, RELU>(m, make(SrcT<4, true>{}), y, ldy, F, stream, ws);
-  auto src = make(SrcT<4, false>{});
-  src.F = (F + 3) & ~3;  // the width the loads may cover; F bounds the stores
-  return launch_vec4<SrcT<4, false>, RELU>(m, src, y, ldy, F, stream, ws);
+// Rows of at least 4 features take 4 per lane, whatever their alignment.
+template <template <int> class SrcT, bool RELU = false, class Make>
+gcn_status dispatch(const Mat& m, int F, float* y, int64_t ldy, hipStream_t stream, Make make,
+                    float* ws = nullptr) {
+  if (F < 4) return launch_all<1, 4, RELU>(m, make(SrcT<1>{}), y, ldy, F, stream, ws);
+  return launch_vec4<SrcT<4>, RELU>(m, make(SrcT<4>{}), y, ldy, F, stream, ws);
 }
-
-bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
 gcn_status check_common(const gcn_graph* g, int64_t F) {
   GCN_CHECK(check_graph(g));
@@ -842,23 +823,14 @@ gcn_status aggregate(const Mat& m, const void* X, int64_t ldx, int dtype, float*
   GCN_CHECK(check_plain(X, ldx, dtype, Y, ldy, F));
   const int Fi = (int)F;
   hipStream_t s = (hipStream_t)stream;
-  const bool yvec = aligned(Y, 16) && ldy % 4 == 0;
-  if (dtype == GCN_DT_F32) {
-    const bool vec4 = yvec && aligned(X, 16) && ldx % 4 == 0;
-    return dispatch<SrcF32>(m, vec4, Fi, Y, ldy, s, [&](auto t) {
-      t.x = (const float*)X;
-      t.ld = (uint32_t)ldx;
-      t.F = Fi;
-      return t;
-    }, false, ws);
-  }
-  const bool vec4 = yvec && aligned(X, 8) && ldx % 4 == 0;
-  return dispatch<SrcBF16>(m, vec4, Fi, Y, ldy, s, [&](auto t) {
-    t.x = (const uint16_t*)X;
+  auto make = [&](auto t) {
+    t.x = static_cast<decltype(t.x)>(X);
     t.ld = (uint32_t)ldx;
     t.F = Fi;
     return t;
-  }, false, ws);
+  };
+  if (dtype == GCN_DT_F32) return dispatch<SrcF32>(m, Fi, Y, ldy, s, make, ws);
+  return dispatch<SrcBF16>(m, Fi, Y, ldy, s, make, ws);
 }
 
 }  // namespace
@@ -866,17 +838,14 @@ gcn_status aggregate(const Mat& m, const void* X, int64_t ldx, int dtype, float*
 gcn_status aggregate_f32(const Mat& m, const float* X, int64_t ldx, float* Y, int64_t ldy,
                          int64_t F, bool relu, hipStream_t stream) {
   const int Fi = (int)F;
-  const bool vec4 = aligned(Y, 16) && ldy % 4 == 0 && aligned(X, 16) && ldx % 4 == 0;
   auto make = [&](auto t) {
     t.x = X;
     t.ld = (uint32_t)ldx;
     t.F = Fi;
     return t;
   };
-  // the training steps keep their feature rows at strides of a multiple of 4
-  const bool pad_ok = ldx >= ((F + 3) & ~int64_t(3));
-  return relu ? dispatch<SrcF32, true>(m, vec4, Fi, Y, ldy, stream, make, pad_ok)
-              : dispatch<SrcF32, false>(m, vec4, Fi, Y, ldy, stream, make, pad_ok);
+  return relu ? dispatch<SrcF32, true>(m, Fi, Y, ldy, stream, make)
+              : dispatch<SrcF32, false>(m, Fi, Y, ldy, stream, make);
 }
 
 }  // namespace gcn
@@ -938,9 +907,6 @@ extern "C" gcn_status gcn_aggregate_fwd_q8halo(const gcn_graph* g, int64_t n_loc
     return GCN_EINVAL;
   }
   const int Fi = (int)F;
-  const bool vec4 = aligned(Y, 16) && ldy % 4 == 0 && (n_local_cols == 0 ||
-                    (aligned(X_local, 16) && ldx % 4 == 0)) &&
-                    (n_local_cols == n_in || two_bit || (aligned(Q_halo, 4) && ldq % 4 == 0));
   auto make = [&](auto t) {
     t.x = X_local;
     t.ldx = (uint32_t)ldx;
@@ -953,8 +919,11 @@ extern "C" gcn_status gcn_aggregate_fwd_q8halo(const gcn_graph* g, int64_t n_loc
     t.F = Fi;
     return t;
   };
-  if (two_bit) return dispatch<SrcQ2>(m, vec4, Fi, Y, ldy, (hipStream_t)stream, make);
-  return dispatch<SrcQ8>(m, vec4, Fi, Y, ldy, (hipStream_t)stream, make);
+  const hipStream_t s = (hipStream_t)stream;
+  if (two_bit)
+    return F % 4 ? dispatch<SrcQ2Tail>(m, Fi, Y, ldy, s, make)
+                 : dispatch<SrcQ2>(m, Fi, Y, ldy, s, make);
+  return dispatch<SrcQ8>(m, Fi, Y, ldy, s, make);
 }
 
 // ---- the aggregation without allocation -------------------------------------
