@@ -53,7 +53,7 @@ MODEL_NOTE = ("no-reuse gather model: every stored entry brings its source row, 
 
 # kernel name -> row-length classes whose rows it processes
 KERNEL_CLASSES = {"agg_zero_rows": [0], "agg_tiny": [1, 2], "agg_short": [3, 4, 5, 6, 7],
-                  "agg_chunk": [8], "agg_pieces": [9]}
+                  "agg_chunk": [8], "agg_pieces": [9], "agg_rows": [0, 1, 2, 3, 4, 5, 6, 7, 8]}
 
 
 def log(msg):

@@ -34,6 +34,9 @@
 //                              (k_chunk)
 //    A last kernel sums each cut row's partial rows in a fixed order
 //    (k_reduce_parts).
+//    Matrices that are not column-blocked and not large run all their rows in
+//    one launch, where the longer rows take a wavefront each (k_rows,
+//    k_rows_small; the rule stands at launch_all).
 //  * Every output element is summed in an order fixed by the graph and F:
 //    no atomics, identical bits on every run.
 //  * Source rows are gathered with 16-byte loads; the (column, value) pair
@@ -393,18 +396,21 @@ constexpr int kSlotClasses = kMedium - kFirstShort + 1;
 struct ShortArgs {
   int64_t row_off[kSlotClasses + 1];   // rows of class kFirstShort + k start at row_off[k]
   int64_t wave_off[kSlotClasses + 1];  // first wavefront of each class; [kSlotClasses] = total
+  int64_t skip;                        // first rows of the last class that others take
 };
 
 // ---- kernels ---------------------------------------------------------------------
 
-// Zero rows that have no entries.
+// The work of one wavefront (of one workgroup for a chunk), shared by the
+// kernels of a class each and by the one that runs them all.
+
+// Zero rows that have no entries (E per wavefront).
 template <int VEC, int G>
-__global__ __launch_bounds__(kBlock) void k_zero_rows(const int32_t* __restrict__ rows,
-                                                      int64_t n, float* __restrict__ y,
-                                                      int64_t ldy, int F) {
+__device__ inline void zero_rows(int64_t wave, const int32_t* __restrict__ rows, int64_t n,
+                                 float* __restrict__ y, int64_t ldy, int F) {
   constexpr int E = 64 / G;
   const int lane = threadIdx.x & 63;
-  const int64_t i = ((int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6)) * E + lane / G;
+  const int64_t i = wave * E + lane / G;
   const int f0 = (int)blockIdx.y * G * VEC + (lane % G) * VEC;
   if (i >= n || f0 >= F) return;
   float z[VEC];
@@ -419,17 +425,15 @@ __global__ __launch_bounds__(kBlock) void k_zero_rows(const int32_t* __restrict_
 // loads (row id and start, entries, feature rows) behind, so the wavefront
 // keeps R * L gathers per lane in flight instead of L; the plan stores their
 // starts next to their ids (beg[i] for rows[i]). The terms of a row are added
-// in entry order, as in k_short.
+// in entry order, as in short_rows.
 template <int VEC, int G, class Src, bool RELU, int L, int R>
-__global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_tiny(const int64_t* __restrict__ beg,
-                                                  const Ent* __restrict__ ent,
-                                                  const int32_t* __restrict__ rows, int64_t n,
-                                                  Src src, float* __restrict__ y, int64_t ldy,
-                                                  int F) {
+__device__ inline void tiny_rows(int64_t wave, const int64_t* __restrict__ beg,
+                                 const Ent* __restrict__ ent, const int32_t* __restrict__ rows,
+                                 int64_t n, const Src& src, float* __restrict__ y, int64_t ldy,
+                                 int F) {
   constexpr int E = 64 / G;
   const int lane = threadIdx.x & 63;
   const int slot = lane / G;
-  const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   const int f0 = (int)blockIdx.y * G * VEC + (lane % G) * VEC;
   const bool fa = f0 < F;
   const int fs = src.clamp(f0);
@@ -477,23 +481,21 @@ __global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_tiny(const int64_t* _
 // per wavefront, the rows of one wavefront from one length class and, within
 // it, of about the same length (the plan orders them by decreasing length).
 template <int VEC, int G, class Src, bool RELU>
-__global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_short(const int64_t* __restrict__ rbeg,
-                                                  const int32_t* __restrict__ rlen,
-                                                  const Ent* __restrict__ ent,
-                                                  const int32_t* __restrict__ rows, ShortArgs sa,
-                                                  Src src, float* __restrict__ y, int64_t ldy,
-                                                  int F) {
+__device__ inline void short_rows(int64_t wave, const int64_t* __restrict__ rbeg,
+                                  const int32_t* __restrict__ rlen, const Ent* __restrict__ ent,
+                                  const int32_t* __restrict__ rows, const ShortArgs& sa,
+                                  const Src& src, float* __restrict__ y, int64_t ldy, int F) {
   constexpr int E = 64 / G;
   constexpr int NS = kSlotClasses;
   const int lane = threadIdx.x & 63;
   const int slot = lane / G, gl = lane % G;
-  const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
   if (wave >= sa.wave_off[NS]) return;  // whole wavefront leaves together
   int c = 0;
 #pragma unroll
   for (int k = 1; k < NS; ++k)
     if (wave >= sa.wave_off[k]) c = k;
-  const int64_t i = sa.row_off[c] + (wave - sa.wave_off[c]) * E + slot;
+  const int64_t i =
+      sa.row_off[c] + (c == NS - 1 ? sa.skip : 0) + (wave - sa.wave_off[c]) * E + slot;
   const int f0 = (int)blockIdx.y * G * VEC + gl * VEC;
   const bool has_row = i < sa.row_off[c + 1];
   const bool active = has_row && f0 < F;
@@ -510,32 +512,34 @@ __global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_short(const int64_t* 
   if (active) store_row<VEC, RELU>(y + (int64_t)r * ldy, src.clamp(f0), acc);
 }
 
-// One workgroup per chunk of a long row. Wavefront w of the workgroup takes
-// the chunk's 64-entry blocks w, w + 4, w + 8, ...; wavefront sums meet in
-// LDS and are added in wavefront order. Single-chunk rows write Y, others a
-// partial row.
-template <int VEC, int G, class Src, bool RELU>
-__global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_chunk(const Ent* __restrict__ ent,
-                                                  const int32_t* __restrict__ chunk_row,
-                                                  const int64_t* __restrict__ chunk_beg,
-                                                  const int64_t* __restrict__ chunk_end,
-                                                  const int32_t* __restrict__ chunk_part, Src src,
-                                                  float* __restrict__ y, int64_t ldy,
-                                                  float* __restrict__ parts, int64_t ldp, int F) {
-  __shared__ float red[kWavesPerBlock][G * VEC];
+struct ChunkArgs {
+  const int32_t* row;
+  const int64_t* beg;
+  const int64_t* end;
+  const int32_t* part;
+  float* parts;
+  int64_t ldp;
+};
+
+// One workgroup of W wavefronts per chunk of a long row. Wavefront w of the
+// workgroup takes the chunk's 64-entry blocks w, w + W, w + 2 W, ...;
+// wavefront sums meet in LDS and are added in wavefront order. Single-chunk
+// rows write Y, others a partial row.
+template <int VEC, int G, class Src, bool RELU, int W, int U>
+__device__ inline void chunk_rows(int64_t c, const Ent* __restrict__ ent, const ChunkArgs& ca,
+                                  const Src& src, float* __restrict__ y, int64_t ldy, int F,
+                                  float (*red)[G * VEC]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = lane / G, gl = lane % G;
-  const int64_t c = blockIdx.x;
-  const int32_t r = chunk_row[c];
-  const int64_t beg = chunk_beg[c];
-  const int64_t end = chunk_end[c];
+  const int32_t r = ca.row[c];
+  const int64_t beg = ca.beg[c];
+  const int64_t end = ca.end[c];
   const int f0 = (int)blockIdx.y * G * VEC + gl * VEC;
   const bool active = f0 < F;
   float acc[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
-  accumulate_blocks<VEC, G, GCN_AGG_UNROLL>(ent, beg, end, wave, kWavesPerBlock, src, f0, active,
-                                            acc);
+  accumulate_blocks<VEC, G, U>(ent, beg, end, wave, W, src, f0, active, acc);
   reduce_slots<VEC, G>(acc);
   if (slot == 0) {
 #pragma unroll
@@ -547,15 +551,147 @@ __global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_chunk(const Ent* __re
     for (int v = 0; v < VEC; ++v) {
       float s = red[0][gl * VEC + v];
 #pragma unroll
-      for (int w = 1; w < kWavesPerBlock; ++w) s += red[w][gl * VEC + v];
+      for (int w = 1; w < W; ++w) s += red[w][gl * VEC + v];
       acc[v] = s;
     }
-    const int32_t part = chunk_part[c];
+    const int32_t part = ca.part[c];
     if (part < 0)
       store_row<VEC, RELU>(y + (int64_t)r * ldy, src.clamp(f0), acc);
     else
-      store_row<VEC>(parts + (int64_t)part * ldp, src.clamp(f0), acc);
+      store_row<VEC>(ca.parts + (int64_t)part * ca.ldp, src.clamp(f0), acc);
   }
+}
+
+__device__ inline int64_t wave_index() {
+  return (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+}
+
+template <int VEC, int G>
+__global__ __launch_bounds__(kBlock) void k_zero_rows(const int32_t* __restrict__ rows, int64_t n,
+                                                      float* __restrict__ y, int64_t ldy, int F) {
+  zero_rows<VEC, G>(wave_index(), rows, n, y, ldy, F);
+}
+
+template <int VEC, int G, class Src, bool RELU, int L, int R>
+__global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_tiny(const int64_t* __restrict__ beg,
+                                                                const Ent* __restrict__ ent,
+                                                                const int32_t* __restrict__ rows,
+                                                                int64_t n, Src src,
+                                                                float* __restrict__ y, int64_t ldy,
+                                                                int F) {
+  tiny_rows<VEC, G, Src, RELU, L, R>(wave_index(), beg, ent, rows, n, src, y, ldy, F);
+}
+
+template <int VEC, int G, class Src, bool RELU>
+__global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_short(const int64_t* __restrict__ rbeg,
+                                                                 const int32_t* __restrict__ rlen,
+                                                                 const Ent* __restrict__ ent,
+                                                                 const int32_t* __restrict__ rows,
+                                                                 ShortArgs sa, Src src,
+                                                                 float* __restrict__ y, int64_t ldy,
+                                                                 int F) {
+  short_rows<VEC, G, Src, RELU>(wave_index(), rbeg, rlen, ent, rows, sa, src, y, ldy, F);
+}
+
+template <int VEC, int G, class Src, bool RELU>
+__global__ __launch_bounds__(kBlock, GCN_MIN_WAVES) void k_chunk(const Ent* __restrict__ ent,
+                                                                 ChunkArgs ca, Src src,
+                                                                 float* __restrict__ y,
+                                                                 int64_t ldy, int F) {
+  __shared__ float red[kWavesPerBlock][G * VEC];
+  chunk_rows<VEC, G, Src, RELU, kWavesPerBlock, GCN_AGG_UNROLL>(blockIdx.x, ent, ca, src, y, ldy, F,
+                                                                red);
+}
+
+// One row per wavefront: its E slots share the entries (accumulate_blocks),
+// U gathers in flight per lane.
+template <int VEC, int G, class Src, bool RELU, int U>
+__device__ inline void wave_row(int32_t r, int64_t b, int64_t e, const Ent* __restrict__ ent,
+                                const Src& src, float* __restrict__ y, int64_t ldy, int F) {
+  const int lane = threadIdx.x & 63;
+  const int f0 = (int)blockIdx.y * G * VEC + (lane % G) * VEC;
+  float acc[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
+  accumulate_blocks<VEC, G, U>(ent, b, e, 0, 1, src, f0, f0 < F, acc);
+  reduce_slots<VEC, G>(acc);
+  if (lane < G && f0 < F) store_row<VEC, RELU>(y + (int64_t)r * ldy, src.clamp(f0), acc);
+}
+
+// All rows of a matrix that is not column-blocked in one launch: workgroups
+// [0, chunk) take the chunks, then come the rows of over kLongRow entries (of
+// over 32 where a slot is at most 8 lanes, which also fetch few entries at a
+// time), a wavefront each, the other rows by slot, and the two-entry, one-entry and
+// empty rows.
+struct RowsArgs {
+  const Ent* ent;
+  const int32_t* rows;   // all rows by class
+  const int64_t* rbeg;   // of the rows from class kFirstShort on
+  const int32_t* rlen;
+  int64_t n0, n1, n2;    // rows of no, one and two entries (in that order in rows)
+  int64_t n_rowk;        // rows of the classes up to kMedium that have entries
+  int64_t first_long, n_long;  // the medium rows that take a wavefront each
+  int64_t chunk, medium, slots, two, one;  // first workgroup past each group
+  ShortArgs sa;
+  ChunkArgs ca;
+};
+
+constexpr int kRowsWaves = 8;
+
+template <int VEC, int G, class Src, bool RELU>
+__global__ __launch_bounds__(64 * kRowsWaves, GCN_MIN_WAVES) void k_rows(RowsArgs a, Src src,
+                                                                float* __restrict__ y, int64_t ldy,
+                                                                int F) {
+  __shared__ float red[kRowsWaves][G * VEC];
+  const int64_t bx = blockIdx.x, w = threadIdx.x >> 6;
+  if (bx < a.chunk) {
+    chunk_rows<VEC, G, Src, RELU, kRowsWaves, GCN_SLOT_UNROLL>(bx, a.ent, a.ca, src, y, ldy, F,
+                                                                  red);
+  } else if (bx < a.medium) {
+    const int64_t k = (bx - a.chunk) * kRowsWaves + w;
+    if (k >= a.n_long) return;  // whole wavefront
+    const int64_t i = a.first_long + k;
+    const int64_t b = a.rbeg[i - a.n0];
+    wave_row<VEC, G, Src, RELU, GCN_SLOT_UNROLL>(a.rows[i], b, b + a.rlen[i - a.n0], a.ent, src, y,
+                                                 ldy, F);
+  } else if (bx < a.slots) {
+    // the last class (the longest rows) first
+    const int64_t back = (a.slots - 1 - bx) * kRowsWaves + w;
+    short_rows<VEC, G, Src, RELU>(back, a.rbeg, a.rlen, a.ent, a.rows, a.sa, src, y, ldy, F);
+  } else if (bx < a.two) {
+    tiny_rows<VEC, G, Src, RELU, 2, GCN_TINY_GROUPS2>((bx - a.slots) * kRowsWaves + w,
+                                                      a.rbeg + a.n1, a.ent, a.rows + a.n0 + a.n1,
+                                                      a.n2, src, y, ldy, F);
+  } else if (bx < a.one) {
+    tiny_rows<VEC, G, Src, RELU, 1, GCN_TINY_GROUPS1>((bx - a.two) * kRowsWaves + w, a.rbeg,
+                                                      a.ent, a.rows + a.n0, a.n1, src, y, ldy, F);
+  } else {
+    zero_rows<VEC, G>((bx - a.one) * kRowsWaves + w, a.rows, a.n0, y, ldy, F);
+  }
+}
+
+// The same for a matrix of so few rows that wavefronts for each are all in
+// flight at once (up to 4,096 rows and feature tiles: 16 wavefronts per CU): time is then the longest chain of dependent loads, so a row
+// takes a whole wavefront (kSmallUnroll gathers in flight per lane) and a chunk kSmallWaves of them.
+constexpr int kSmallWaves = 8;
+constexpr int kSmallUnroll = 8;
+
+template <int VEC, int G, class Src, bool RELU>
+__global__ __launch_bounds__(64 * kSmallWaves) void k_rows_small(RowsArgs a, Src src,
+                                                                 float* __restrict__ y,
+                                                                 int64_t ldy, int F) {
+  __shared__ float red[kSmallWaves][G * VEC];
+  const int64_t bx = blockIdx.x;
+  if (bx < a.chunk) {
+    chunk_rows<VEC, G, Src, RELU, kSmallWaves, kSmallUnroll>(bx, a.ent, a.ca, src, y, ldy, F, red);
+    return;
+  }
+  // long rows first: the row tables run from no entries to the medium class
+  const int64_t i = a.n0 + a.n_rowk - 1 - ((bx - a.chunk) * kSmallWaves + (threadIdx.x >> 6));
+  if (i < 0) return;  // whole wavefront
+  const int64_t b = i >= a.n0 ? a.rbeg[i - a.n0] : 0;
+  const int64_t e = i >= a.n0 ? b + a.rlen[i - a.n0] : 0;
+  wave_row<VEC, G, Src, RELU, kSmallUnroll>(a.rows[i], b, e, a.ent, src, y, ldy, F);
 }
 
 // Column-blocked pieces (at most piece_max entries each), one per slot, in
@@ -641,6 +777,8 @@ __global__ __launch_bounds__(kBlock) void k_reduce_parts(const int32_t* __restri
 
 // ---- launch ------------------------------------------------------------------------
 
+constexpr int64_t kFusedGathers = 800000000;  // entries x features
+
 inline unsigned blocks_for_waves(int64_t waves) {
   return (unsigned)std::max<int64_t>(1, ceil_div(waves, kWavesPerBlock));
 }
@@ -653,27 +791,89 @@ gcn_status launch_all(const Mat& m, const Src& src, float* y, int64_t ldy, int F
   constexpr int E = 64 / G;
   const Plan& p = m.plan;
   const unsigned tiles = (unsigned)ceil_div(F, G * VEC);
-  // empty rows
   const int64_t n_empty = p.class_off[kClassEmpty + 1] - p.class_off[kClassEmpty];
-  if (n_empty > 0) {
-    ProfScope ps("agg_zero_rows", stream);
-    hipLaunchKernelGGL((k_zero_rows<VEC, G>), dim3(blocks_for_waves(ceil_div(n_empty, E)), tiles),
-                       dim3(kBlock), 0, stream, (const int32_t*)(p.rows + p.class_off[kClassEmpty]),
-                       n_empty, y, ldy, F);
-    GCN_HIP(hipGetLastError());
+  const int64_t n1 = p.class_off[kFirstShort + 1] - p.class_off[kFirstShort];
+  const int64_t n2 = p.class_off[kFirstShort + 2] - p.class_off[kFirstShort + 1];
+  constexpr int R1 = GCN_TINY_GROUPS1, R2 = GCN_TINY_GROUPS2;
+  // rows of 3 .. medium_max entries (the classes of one and two entries get no
+  // waves here)
+  ShortArgs sa{};
+  int64_t waves = 0;
+  for (int c = kFirstShort; c <= kMedium + 1; ++c) {
+    sa.row_off[c - kFirstShort] = p.class_off[c];
+    sa.wave_off[c - kFirstShort] = waves;
+    if (c >= kFirstShort + 2 && c <= kMedium)
+      waves += ceil_div(p.class_off[c + 1] - p.class_off[c], E);
   }
-  // rows of exactly one and exactly two entries
-  {
-    const int64_t n1 = p.class_off[kFirstShort + 1] - p.class_off[kFirstShort];
-    const int64_t n2 = p.class_off[kFirstShort + 2] - p.class_off[kFirstShort + 1];
-    constexpr int R1 = GCN_TINY_GROUPS1, R2 = GCN_TINY_GROUPS2;
+  float* parts = ws;
+  const int64_t ldp = (F + 3) & ~3;
+  if (p.n_parts > 0 && !ws) GCN_CHECK(talloc(&parts, p.n_parts * ldp, stream, "partial rows"));
+  // a workspace the caller owns is never released here
+  auto release = [&]() {
+    if (!ws) tfree(parts, stream);
+  };
+  const ChunkArgs ca{p.chunk_row, p.chunk_beg, p.chunk_end, p.chunk_part, parts, ldp};
+  hipError_t e = hipSuccess;
+  // Where one launch for all rows pays (us per pass, power-law graphs of 16 or
+  // 48 entries a row; a launch per class -> this): the slots' chains of up to
+  // 256 entries, and the gaps between five launches, set the time (1,024 x 64: 26
+  // -> 8; 4,096 x 128: 40 -> 10; 32,768 x 16: 80 -> 15; 65,536 x 128: 89 -> 41;
+  // 170,003 x 47: 111 -> 66; 65,536 x 256, 6.7e8 features gathered: 191 -> 161).
+  // From about 8e8 on each class fills the chip by itself, and together they
+  // disturb each other's rows in the caches (170,003 x 256, 48 a row: 540 ->
+  // 590). Graphs without long rows have neither chain nor launches to save
+  // (uniform, 33 a row, 32,768 x 256: 118 -> 122) unless all their rows are in
+  // flight at once (4,096 x 64: the kernel 9 -> 4).
+  const bool long_rows = p.n_chunks > 0 || p.n_long > 0;
+  const bool all_in_flight = m.n_major * tiles <= 4096;
+  if (p.n_pieces == 0 && m.nnz <= kFusedGathers / F && (long_rows || all_in_flight)) {
+    RowsArgs a{};
+    a.ent = m.ent;
+    a.rows = p.rows;
+    a.rbeg = p.rbeg;
+    a.rlen = p.rlen;
+    a.n0 = n_empty;
+    a.n1 = n1;
+    a.n2 = n2;
+    a.n_rowk = p.class_off[kMedium + 1] - p.class_off[kFirstShort];
+    a.sa = sa;
+    a.ca = ca;
+    a.chunk = p.n_chunks;
+    ProfScope ps("agg_rows", stream);
+    if (all_in_flight) {
+      const int64_t nb = p.n_chunks + ceil_div(a.n0 + a.n_rowk, (int64_t)kSmallWaves);
+      hipLaunchKernelGGL((k_rows_small<VEC, G, Src, RELU>), dim3((unsigned)nb, tiles),
+                         dim3(64 * kSmallWaves), 0, stream, a, src, y, ldy, F);
+    } else {
+      const int64_t wpb = kRowsWaves;
+      const int64_t n_medium = p.class_off[kMedium + 1] - p.class_off[kMedium];
+      a.first_long = p.class_off[kMedium];
+      a.n_long = G <= 8 ? n_medium : p.n_long;
+      // the rows after them keep their slots
+      waves += ceil_div(n_medium - a.n_long, E) - ceil_div(n_medium, E);
+      a.sa.skip = a.n_long;
+      a.sa.wave_off[kSlotClasses] = waves;
+      a.medium = a.chunk + ceil_div(a.n_long, wpb);
+      a.slots = a.medium + ceil_div(waves, wpb);
+      a.two = a.slots + ceil_div(ceil_div(n2, (int64_t)E * R2), wpb);
+      a.one = a.two + ceil_div(ceil_div(n1, (int64_t)E * R1), wpb);
+      const int64_t nb = a.one + ceil_div(ceil_div(n_empty, (int64_t)E), wpb);
+      hipLaunchKernelGGL((k_rows<VEC, G, Src, RELU>), dim3((unsigned)nb, tiles),
+                         dim3(64 * kRowsWaves), 0, stream, a, src, y, ldy, F);
+    }
+    e = hipGetLastError();
+  } else {
+    if (n_empty > 0) {
+      ProfScope ps("agg_zero_rows", stream);
+      hipLaunchKernelGGL((k_zero_rows<VEC, G>), dim3(blocks_for_waves(ceil_div(n_empty, E)), tiles),
+                         dim3(kBlock), 0, stream, (const int32_t*)p.rows, n_empty, y, ldy, F);
+    }
     if (n1 > 0) {
       ProfScope ps("agg_tiny", stream);
       hipLaunchKernelGGL((k_tiny<VEC, G, Src, RELU, 1, R1>),
                          dim3(blocks_for_waves(ceil_div(n1, E * R1)), tiles), dim3(kBlock), 0,
                          stream, (const int64_t*)p.rbeg, (const Ent*)m.ent,
                          (const int32_t*)(p.rows + p.class_off[kFirstShort]), n1, src, y, ldy, F);
-      GCN_HIP(hipGetLastError());
     }
     if (n2 > 0) {
       ProfScope ps("agg_tiny", stream);
@@ -682,74 +882,39 @@ gcn_status launch_all(const Mat& m, const Src& src, float* y, int64_t ldy, int F
                          stream, (const int64_t*)(p.rbeg + n1), (const Ent*)m.ent,
                          (const int32_t*)(p.rows + p.class_off[kFirstShort + 1]), n2, src, y, ldy,
                          F);
-      GCN_HIP(hipGetLastError());
     }
-  }
-  // rows of 3 .. medium_max entries (the classes of one and two entries get no
-  // waves here)
-  ShortArgs sa;
-  int64_t waves = 0;
-  for (int c = kFirstShort; c <= kMedium + 1; ++c) {
-    sa.row_off[c - kFirstShort] = p.class_off[c];
-    sa.wave_off[c - kFirstShort] = waves;
-    if (c >= kFirstShort + 2 && c <= kMedium)
-      waves += ceil_div(p.class_off[c + 1] - p.class_off[c], E);
-  }
-  if (waves > 0) {
-    ProfScope ps("agg_short", stream);
-    hipLaunchKernelGGL((k_short<VEC, G, Src, RELU>), dim3(blocks_for_waves(waves), tiles),
-                       dim3(kBlock), 0, stream, (const int64_t*)p.rbeg, (const int32_t*)p.rlen,
-                       (const Ent*)m.ent, (const int32_t*)p.rows, sa, src, y, ldy, F);
-    GCN_HIP(hipGetLastError());
-  }
-  // long rows: chunk table, then column-blocked pieces, then the partial sums
-  if (p.n_chunks > 0 || p.n_pieces > 0) {
-    float* parts = ws;
-    const int64_t ldp = (F + 3) & ~3;
-    if (p.n_parts > 0 && !ws) GCN_CHECK(talloc(&parts, p.n_parts * ldp, stream, "partial rows"));
-    // a workspace the caller owns is never released here
-    auto release = [&]() {
-      if (!ws) tfree(parts, stream);
-    };
+    if (waves > 0) {
+      ProfScope ps("agg_short", stream);
+      hipLaunchKernelGGL((k_short<VEC, G, Src, RELU>), dim3(blocks_for_waves(waves), tiles),
+                         dim3(kBlock), 0, stream, (const int64_t*)p.rbeg, (const int32_t*)p.rlen,
+                         (const Ent*)m.ent, (const int32_t*)p.rows, sa, src, y, ldy, F);
+    }
     if (p.n_chunks > 0) {
       ProfScope ps("agg_chunk", stream);
       hipLaunchKernelGGL((k_chunk<VEC, G, Src, RELU>), dim3((unsigned)p.n_chunks, tiles),
-                         dim3(kBlock), 0, stream, (const Ent*)m.ent, (const int32_t*)p.chunk_row,
-                         (const int64_t*)p.chunk_beg, (const int64_t*)p.chunk_end,
-                         (const int32_t*)p.chunk_part, src, y, ldy, parts, ldp, F);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) {
-        release();
-        return hip_fail(e, "k_chunk", __FILE__, __LINE__);
-      }
+                         dim3(kBlock), 0, stream, (const Ent*)m.ent, ca, src, y, ldy, F);
     }
-    if (p.n_pieces > 0) {
+    e = hipGetLastError();
+    if (e == hipSuccess && p.n_pieces > 0) {
       ProfScope ps("agg_pieces", stream);
       hipLaunchKernelGGL((k_pieces<VEC, G, Src>),
                          dim3(blocks_for_waves(ceil_div(p.n_pieces, E)), tiles),
                          dim3(kBlock), 0, stream, (const int64_t*)p.piece_beg,
                          (const int32_t*)p.piece_len, (const int32_t*)p.piece_part, p.n_pieces,
                          (const Ent*)m.ent, src, parts, ldp, F);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) {
-        release();
-        return hip_fail(e, "k_pieces", __FILE__, __LINE__);
-      }
+      e = hipGetLastError();
     }
-    if (p.n_giant > 0) {
-      ProfScope ps("agg_reduce_parts", stream);
-      hipLaunchKernelGGL((k_reduce_parts<VEC, G, RELU>), dim3(blocks_for_waves(p.n_giant), tiles),
-                         dim3(kBlock), 0, stream, (const int32_t*)p.giant_row,
-                         (const int32_t*)p.giant_part_off, p.n_giant, (const float*)parts, ldp, y,
-                         ldy, F);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) {
-        release();
-        return hip_fail(e, "k_reduce_parts", __FILE__, __LINE__);
-      }
-    }
-    release();
   }
+  if (e == hipSuccess && p.n_giant > 0) {
+    ProfScope ps("agg_reduce_parts", stream);
+    hipLaunchKernelGGL((k_reduce_parts<VEC, G, RELU>), dim3(blocks_for_waves(p.n_giant), tiles),
+                       dim3(kBlock), 0, stream, (const int32_t*)p.giant_row,
+                       (const int32_t*)p.giant_part_off, p.n_giant, (const float*)parts, ldp, y,
+                       ldy, F);
+    e = hipGetLastError();
+  }
+  release();
+  if (e != hipSuccess) return hip_fail(e, "aggregation", __FILE__, __LINE__);
   return GCN_OK;
 }
 

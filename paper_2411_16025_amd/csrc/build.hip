@@ -137,27 +137,26 @@ __global__ void k_class_keys(const int64_t* __restrict__ ptr, int64_t n_major, i
   keys[r] = ((uint64_t)c << 60) | (lcode << 32) | (uint64_t)r;
 }
 
-// per-class row and entry counts (integer sums, so the atomics are exact)
+// per-class row and entry counts and the medium rows over kLongRow entries
+// (integer sums, so the atomics are exact)
+constexpr int kCounts = 2 * kNumClasses + 1;
+
 __global__ void k_class_count(const int64_t* __restrict__ ptr, int64_t n_major, int64_t medium_max,
                               unsigned long long* __restrict__ counts) {
-  __shared__ unsigned long long rows[kNumClasses], ents[kNumClasses];
-  if (threadIdx.x < kNumClasses) {
-    rows[threadIdx.x] = 0;
-    ents[threadIdx.x] = 0;
-  }
+  __shared__ unsigned long long cnt[kCounts];
+  if (threadIdx.x < kCounts) cnt[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n_major) {
+  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n_major;
+       r += (int64_t)gridDim.x * blockDim.x) {
     const int64_t len = ptr[r + 1] - ptr[r];
     const int c = row_class(len, medium_max);
-    atomicAdd(&rows[c], 1ull);
-    atomicAdd(&ents[c], (unsigned long long)len);
+    atomicAdd(&cnt[c], 1ull);
+    atomicAdd(&cnt[kNumClasses + c], (unsigned long long)len);
+    if (c == kMedium && len > kLongRow) atomicAdd(&cnt[2 * kNumClasses], 1ull);
   }
   __syncthreads();
-  if (threadIdx.x < kNumClasses) {
-    atomicAdd(&counts[threadIdx.x], rows[threadIdx.x]);
-    atomicAdd(&counts[kNumClasses + threadIdx.x], ents[threadIdx.x]);
-  }
+  if (threadIdx.x < kCounts && cnt[threadIdx.x])
+    atomicAdd(&counts[threadIdx.x], cnt[threadIdx.x]);
 }
 
 // first entry and length of each row of a run of `rows`
@@ -587,7 +586,7 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
   unsigned long long* counts = nullptr;
   GCN_CHECK(tmp.alloc(&keys, n, "class keys"));
   GCN_CHECK(tmp.alloc(&sorted, n, "class keys"));
-  GCN_CHECK(tmp.alloc(&counts, 2 * kNumClasses, "class counts"));
+  GCN_CHECK(tmp.alloc(&counts, kCounts, "class counts"));
   {
     Slab slab;
     slab.add(&p.rows, n);
@@ -595,11 +594,11 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
     slab.add(&p.rlen, n);
     GCN_CHECK(slab.alloc(&p.slab, "class rows"));
   }
-  GCN_HIP(hipMemsetAsync(counts, 0, 2 * kNumClasses * sizeof(unsigned long long), stream));
+  GCN_HIP(hipMemsetAsync(counts, 0, kCounts * sizeof(unsigned long long), stream));
   hipLaunchKernelGGL(k_class_keys, dim3(grid_for(n)), dim3(kThreads), 0, stream, m.ptr, n,
                      p.medium_max, keys);
   GCN_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_class_count, dim3(grid_for(n)), dim3(kThreads), 0, stream, m.ptr, n,
+  hipLaunchKernelGGL(k_class_count, dim3(std::min(grid_for(n), 1024u)), dim3(kThreads), 0, stream, m.ptr, n,
                      p.medium_max, counts);
   GCN_HIP(hipGetLastError());
   // four stable 8-bit passes over bits [32, 64): by length code, then by class
@@ -610,7 +609,7 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
   hipLaunchKernelGGL(k_low32, dim3(grid_for(n)), dim3(kThreads), 0, stream,
                      (const uint64_t*)keys, n, p.rows);
   GCN_HIP(hipGetLastError());
-  unsigned long long host_counts[2 * kNumClasses];
+  unsigned long long host_counts[kCounts];
   GCN_HIP(hipMemcpyAsync(host_counts, counts, sizeof(host_counts), hipMemcpyDeviceToHost, stream));
   GCN_HIP(hipStreamSynchronize(stream));
   p.class_off[0] = 0;
@@ -618,6 +617,7 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
     p.class_off[c + 1] = p.class_off[c] + (int64_t)host_counts[c];
     p.class_nnz[c] = (int64_t)host_counts[kNumClasses + c];
   }
+  p.n_long = (int64_t)host_counts[2 * kNumClasses];
   // rows up to the medium class read their start and length from here (one
   // load fewer in their chain of dependent loads)
   const int64_t n_rowk = p.class_off[kMedium + 1] - p.class_off[kFirstShort];

@@ -34,6 +34,7 @@ constexpr int kFirstShort = 1;
 constexpr int kLastShort = 6;
 constexpr int kMedium = 7;
 constexpr int kChunked = 8;
+constexpr int64_t kLongRow = 64;  // see k_rows in aggregate.hip
 
 struct Plan {
   void* slab = nullptr;      // the one allocation that holds rows, rbeg and rlen
@@ -46,6 +47,7 @@ struct Plan {
   int32_t* rlen = nullptr;
   int64_t class_off[kNumClasses + 1] = {};  // host copy of the class boundaries in `rows`
   int64_t class_nnz[kNumClasses] = {};      // host: stored entries per class
+  int64_t n_long = 0;                       // host: rows of the medium class over kLongRow entries
   int64_t medium_max = 48;                  // longest row of the medium class (256 unblocked)
   int64_t chunk_len = 2048;                 // entries per chunk of a chunked row
   // chunk table for rows of the chunked class
