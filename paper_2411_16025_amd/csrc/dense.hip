@@ -5,7 +5,7 @@
 // GEMM shapes of full-batch GCN training are tall and skinny: the node count
 // is in the millions, feature and class counts are at most a few hundred.
 //  * C = A op(B) with M = nodes (NN, NT): one 256-thread workgroup computes a
-//    64 x BN tile of C (BN = 64, 128 or 256) over all of K, staging 32-deep
+//    64 x BN tile of C (BN = 48, 64 or 128) over all of K, staging 32-deep
 //    slices of A and B in LDS while the next slice is loaded into registers;
 //    each wavefront owns 16 rows and issues v_mfma_f32_16x16x4_f32 on BN / 16
 //    blocks of 16 x 16. The tile leaves through LDS as row-contiguous
@@ -184,13 +184,9 @@ __device__ inline f4 load4(const float* __restrict__ p, int64_t row, int64_t row
 // B is kept k-major for NN and n-major for NT (both written with 16-byte
 // LDS stores). With mask, C = 0 where mask <= 0 (a ReLU backward); with
 // relu, C = max(C, 0) (a ReLU forward).
+// Workgroups per CU the tiles must fit (fewer registers, more waves to overlap LDS and global latency).
 #ifndef GCN_GEMM_MIN_BLOCKS
-#define GCN_GEMM_MIN_BLOCKS 2
-#endif
-// Workgroups per CU the 64- and 128-column tiles must fit (fewer registers,
-// more waves to overlap LDS and global latency).
-#ifndef GCN_GEMM_MIN_BLOCKS_NARROW
-#define GCN_GEMM_MIN_BLOCKS_NARROW 4
+#define GCN_GEMM_MIN_BLOCKS 4
 #endif
 #ifndef GCN_GEMM_KK_UNROLL
 #define GCN_GEMM_KK_UNROLL 8
@@ -203,8 +199,7 @@ __device__ inline f4 load4(const float* __restrict__ p, int64_t row, int64_t row
 constexpr int stride_n(int bn) { return bn + (48 - bn % 32) % 32; }
 
 template <int OP, int BN, int RB>
-__global__ __launch_bounds__(kThreads,
-                             BN == 256 ? GCN_GEMM_MIN_BLOCKS : GCN_GEMM_MIN_BLOCKS_NARROW)
+__global__ __launch_bounds__(kThreads, GCN_GEMM_MIN_BLOCKS)
 void k_gemm_tall_v(int64_t M, int64_t N, int64_t K, const float* __restrict__ A, int64_t lda,
                    const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc,
                    const float* __restrict__ mask, int64_t ldm, bool relu, bool cvec) {
@@ -1520,14 +1515,10 @@ namespace {
 
 bool aligned16(const void* p, int64_t ld) { return ((uintptr_t)p % 16) == 0 && ld % 4 == 0; }
 
-// widest tile of 64, 128 or 256 columns that is not mostly padding
-// Output tile widths. C = A B: 256 columns once N > 128 (A is read once per
-// tile column). C = A B^T and C = A^T B: at most 128 (more workgroups at 4
-// per CU, and less padding of odd widths, outweigh the extra reads of A).
-// Outputs of at most 48 columns (the class count of the training steps, 47)
-// take a 48-column tile: 3 instead of 4 matrix-core blocks per 16 rows.
-int tile_n(int64_t N) { return N <= 48 ? 48 : (N <= 64 ? 64 : (N <= 128 ? 128 : 256)); }
-int tile_n_narrow(int64_t N) { return N <= 48 ? 48 : (N <= 64 ? 64 : 128); }
+// Output tile widths. Outputs of at most 48 columns (the class count of the
+// training steps, 47) take a 48-column tile: 3 instead of 4 matrix-core blocks
+// per 16 rows.
+int tile_n(int64_t N) { return N <= 48 ? 48 : (N <= 64 ? 64 : 128); }
 
 // Compute units of the current device (cached per device).
 int cu_count() {
@@ -1582,7 +1573,7 @@ template <int OP>
 hipError_t launch_tall(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                  int64_t ldb, float* C, int64_t ldc, const float* mask, int64_t ldm,
                  bool relu, hipStream_t stream) {
-  const int bn = OP == kNN ? tile_n(N) : tile_n_narrow(N);
+  const int bn = tile_n(N);
   // staged 16-byte stores need 16-byte aligned rows of C (and of the mask)
   const bool cvec = aligned16(C, ldc) && (!mask || aligned16(mask, ldm));
   // ring: D slots of CPS chunks (D * CPS must divide the chunk count)
@@ -1606,11 +1597,8 @@ hipError_t launch_tall(int64_t M, int64_t N, int64_t K, const float* A, int64_t 
   else if (bn == 64)
     hipLaunchKernelGGL((k_gemm_tall_v<OP, 64, 1>), grid, dim3(kThreads), 0, stream, M, N, K, A,
                        lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
-  else if (OP != kNN || bn == 128)
+  else
     hipLaunchKernelGGL((k_gemm_tall_v<OP, 128, 1>), grid, dim3(kThreads), 0, stream, M, N, K, A,
-                       lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
-  else if constexpr (OP == kNN)
-    hipLaunchKernelGGL((k_gemm_tall_v<OP, 256, 1>), grid, dim3(kThreads), 0, stream, M, N, K, A,
                        lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
   return hipGetLastError();
 }
@@ -1670,7 +1658,7 @@ void launch_tns(const TnsPlan& p, int64_t M, int64_t N, int64_t K, const float* 
 
 }  // namespace
 
-constexpr int64_t kSplitMinWork = 1500000000;  // M N K
+constexpr int64_t kSplitMinWork = 400000000;  // M N K
 constexpr int64_t kSplitMinRows = 4096;
 
 gcn_status sum_partials(int64_t M, int64_t N, int64_t chunks, const float* part, float* C,
@@ -1725,12 +1713,15 @@ gcn_status gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int
     if (relu) GCN_CHECK(relu_fwd(M, N, C, ldc, stream));
     return GCN_OK;
   }
-  // Three-part products on the bf16 matrix cores: outputs of more than 64
-  // columns once the product outweighs packing B (65,536 x 256 x 100: 41 us
-  // against 51; 16,384 x 256 x 100: 35 against 21), and every unaligned one
-  // that is not tiny (the general kernel loads element by element: 500,000 x
-  // 47 x 256 418 us). Narrower aligned outputs are bound by reading A either way.
-  if ((vec ? N > 64 && M * N * K >= kSplitMinWork : M >= kSplitMinRows) &&
+  // Three-part products on the bf16 matrix cores: outputs of more than 128
+  // columns, and of more than 64 once the product outweighs packing B (us, the
+  // tiles here -> three parts: 1,000 x 256 x 100 16.5 -> 13.4, x 516 63 -> 32;
+  // 30,000 x 128 x 256 28 -> 22; 3,000 x 128 x 256 19.6 -> 19.5, x 100 x 64 8.4 ->
+  // 12.2), and every unaligned one that is not tiny (the general kernel loads
+  // element by element: 500,000 x 47 x 256 418 us, 170). Narrower aligned
+  // outputs are bound by reading A either way.
+  const bool outweighs = M * N * K >= kSplitMinWork || (N > 128 && K >= 96 && M >= 256);
+  if ((vec ? N > 64 && outweighs : M >= kSplitMinRows) &&
       gemm_split_tall_takes(M, N, K, lda, ldc, mask ? ldm : 0))
     return gemm_split_tall(op, M, N, K, A, lda, B, ldb, C, ldc, mask, ldm, relu, stream);
   const dim3 grid((unsigned)ceil_div(M, kTile), (unsigned)ceil_div(N, kTile));
