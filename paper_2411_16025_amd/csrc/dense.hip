@@ -1371,13 +1371,20 @@ __global__ void k_zero_count(unsigned long long* __restrict__ cnt) {
 }
 
 // Rows that count in the loss: those with skip[i] == 0 (all rows without a
-// skip array). cnt receives their number (integer atomics: exact).
+// skip array). cnt receives their number (integer atomics, exact; one per
+// workgroup of at most 512: one per wavefront took 33 us on 170,003 rows).
 __global__ __launch_bounds__(kThreads) void k_count_kept(int64_t n, const uint8_t* __restrict__ skip,
                                                          unsigned long long* __restrict__ cnt) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const bool keep = i < n && skip[i] == 0;
-  const unsigned long long b = __ballot(keep);
-  if ((threadIdx.x & 63) == 0 && b) atomicAdd(cnt, (unsigned long long)__popcll(b));
+  __shared__ unsigned int sum;
+  if (threadIdx.x == 0) sum = 0;
+  __syncthreads();
+  unsigned int k = 0;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * kThreads)
+    k += skip[i] == 0;
+  if (k) atomicAdd(&sum, k);
+  __syncthreads();
+  if (threadIdx.x == 0 && sum) atomicAdd(cnt, (unsigned long long)sum);
 }
 
 // Partner of a lane at distance 1, 2, 4 or 8 within its row of 16 lanes:
@@ -1496,7 +1503,16 @@ __global__ __launch_bounds__(kThreads) void k_loss_total(int64_t nb, int64_t n,
                                                          const unsigned long long* __restrict__ n_kept) {
   __shared__ double part[kThreads];
   double s = 0.0;
-  for (int64_t b = threadIdx.x; b < nb; b += kThreads) s += block_loss[b];
+  constexpr int A = 8;  // loads ahead of the additions
+  int64_t b = threadIdx.x;
+  for (; b + (A - 1) * kThreads < nb; b += A * kThreads) {
+    double v[A];
+#pragma unroll
+    for (int k = 0; k < A; ++k) v[k] = block_loss[b + k * kThreads];
+#pragma unroll
+    for (int k = 0; k < A; ++k) s += v[k];
+  }
+  for (; b < nb; b += kThreads) s += block_loss[b];
   part[threadIdx.x] = s;
   __syncthreads();
   for (int off = kThreads / 2; off > 0; off >>= 1) {
@@ -1939,7 +1955,8 @@ gcn_status softmax_xent(int64_t n, int C, const float* z, int64_t ldz, const int
     hipLaunchKernelGGL(k_zero_count, dim3(1), dim3(64), 0, stream, cnt);
     e = hipGetLastError();
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_count_kept, dim3((unsigned)std::max<int64_t>(1, ceil_div(n, kThreads))),
+      hipLaunchKernelGGL(k_count_kept,
+                         dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(512, ceil_div(n, 4 * kThreads)))),
                          dim3(kThreads), 0, stream, n, skip, cnt);
       e = hipGetLastError();
     }

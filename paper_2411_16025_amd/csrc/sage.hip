@@ -257,8 +257,9 @@ __global__ __launch_bounds__(kThreadsS) void k_onehot(int64_t n, int C, int64_t 
 // rows [b R, (b + 1) R) in row order (thread = column, eight rows loaded
 // ahead of the additions), then k_colsum_reduce runs one workgroup per
 // column: thread t adds the partials t, t + 256, ... in turn, and a fixed
-// tree combines the 256 sums.
-constexpr int kColsumRows = 1024;
+// tree combines the 256 sums. 256 rows per workgroup: with 1024 a graph of
+// 170,003 nodes had 167 workgroups (126 us per layer of 256, 38 with 256 rows).
+constexpr int kColsumRows = 256;
 constexpr int kColsumAhead = 8;
 
 __global__ __launch_bounds__(kThreadsS) void k_colsum_partial(int64_t n, int64_t N,
@@ -288,7 +289,15 @@ __global__ __launch_bounds__(kThreadsS) void k_colsum_reduce(int64_t nb, int64_t
   __shared__ float red[kThreadsS];
   const int64_t c = blockIdx.x;
   float s = 0.f;
-  for (int64_t b = threadIdx.x; b < nb; b += kThreadsS) s += part[b * N + c];
+  int64_t b = threadIdx.x;
+  for (; b + (kColsumAhead - 1) * kThreadsS < nb; b += kColsumAhead * kThreadsS) {
+    float v[kColsumAhead];
+#pragma unroll
+    for (int k = 0; k < kColsumAhead; ++k) v[k] = part[(b + k * kThreadsS) * N + c];
+#pragma unroll
+    for (int k = 0; k < kColsumAhead; ++k) s += v[k];
+  }
+  for (; b < nb; b += kThreadsS) s += part[b * N + c];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int off = kThreadsS / 2; off > 0; off >>= 1) {
@@ -312,6 +321,7 @@ struct Layer {
   float* wn = nullptr;    // tf: W_neigh padded to [f x fop]
   float* bc = nullptr;    // tf: [W_self | 0 | W_neigh | 0], [f x 2 fop]
   float* o = nullptr;     // [n x fop] pre-activation; after ReLU the layer output
+  bool own_o = true;      // false: o is the caller's output
 };
 
 inline int64_t round32(int64_t v) { return (v + 31) & ~int64_t(31); }
@@ -365,7 +375,7 @@ void sage_free(Sage& m, hipStream_t s) {
   m.tmid = nullptr;
   tfree(m.xp, s);
   for (int l = 2; l >= 0; --l) {
-    tfree(m.L[l].o, s);
+    if (m.L[l].own_o) tfree(m.L[l].o, s);
     tfree(m.L[l].bc, s);
     tfree(m.L[l].wn, s);
     tfree(m.L[l].wp, s);
@@ -377,11 +387,14 @@ void sage_free(Sage& m, hipStream_t s) {
 }
 
 // Shapes, buffers, packed weights and the forward pass; on return L[2].o
-// holds the logits and L[0..1].o the ReLU outputs of layers 1 and 2.
+// holds the logits and L[0..1].o the ReLU outputs of layers 1 and 2. The
+// caller's H1 and H2 take the place of L[0..1].o where they have their layout
+// (2.45M x 256: a copy of each took 0.9 ms).
 gcn_status sage_forward(const gcn_graph* g, const float* X, int64_t ldx, int64_t f_in,
                         int64_t hidden, int64_t n_classes, const float* const* params,
                         const int32_t* labels, const uint8_t* lp_mask, const float* E, double eps,
-                        Sage& m, hipStream_t s) {
+                        Sage& m, hipStream_t s, float* H1 = nullptr, int64_t ldh1 = 0,
+                        float* H2 = nullptr, int64_t ldh2 = 0) {
   const int64_t n = g->n_rows;
   m.n = n;
   Layer* L = m.L;
@@ -392,7 +405,13 @@ gcn_status sage_forward(const gcn_graph* g, const float* X, int64_t ldx, int64_t
     st = talloc(&L[l].c, n * L[l].ldc, s, "concatenated layer input");
     if (st == GCN_OK) st = talloc(&L[l].rstd, n, s, "LayerNorm 1/std");
     if (st == GCN_OK) st = talloc(&L[l].wp, L[l].K * L[l].fop, s, "packed weights");
-    if (st == GCN_OK) st = talloc(&L[l].o, n * L[l].fop, s, "layer output");
+    float* out = l == 0 ? H1 : (l == 1 ? H2 : nullptr);
+    if (out && (l == 0 ? ldh1 : ldh2) == L[l].fop && reinterpret_cast<uintptr_t>(out) % 16 == 0) {
+      L[l].o = out;
+      L[l].own_o = false;
+    } else if (st == GCN_OK) {
+      st = talloc(&L[l].o, n * L[l].fop, s, "layer output");
+    }
     if (st == GCN_OK && L[l].tf) st = talloc(&L[l].wn, L[l].f * L[l].fop, s, "padded W_neigh");
     if (st == GCN_OK && L[l].tf) st = talloc(&L[l].bc, L[l].f * 2 * L[l].fop, s, "[W_self | W_neigh]");
   }
@@ -678,9 +697,11 @@ extern "C" gcn_status gcn_sage3_forward(const gcn_graph* g, const float* X, int6
   hipStream_t s = (hipStream_t)stream_;
   Sage m;
   gcn_status st = sage_forward(g, X, ldx, f_in, hidden, n_classes, params, labels, lp_mask, E,
-                               eps, m, s);
-  if (st == GCN_OK) st = copy_rows(H1, ldh1, m.L[0].o, m.L[0].fop, m.n, hidden, s);
-  if (st == GCN_OK) st = copy_rows(H2, ldh2, m.L[1].o, m.L[1].fop, m.n, hidden, s);
+                               eps, m, s, H1, ldh1, H2, ldh2);
+  if (st == GCN_OK && m.L[0].own_o)
+    st = copy_rows(H1, ldh1, m.L[0].o, m.L[0].fop, m.n, hidden, s);
+  if (st == GCN_OK && m.L[1].own_o)
+    st = copy_rows(H2, ldh2, m.L[1].o, m.L[1].fop, m.n, hidden, s);
   if (st == GCN_OK) st = copy_rows(logits, ldl, m.L[2].o, m.L[2].fop, m.n, n_classes, s);
   sage_free(m, s);
   return st;
