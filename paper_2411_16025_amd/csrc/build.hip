@@ -50,27 +50,72 @@ __global__ void k_diag_keys(int64_t n_diag, int colbits, uint64_t* __restrict__ 
   if (i < n_diag) keys[i] = ((uint64_t)i << colbits) | (uint64_t)i;
 }
 
-// 1 for the first copy of each distinct valid key in a sorted array.
-struct UniqueFlag {
-  const uint64_t* keys;
-  uint64_t sentinel;
-  __device__ int64_t operator()(int64_t i) const {
-    const uint64_t k = keys[i];
-    return (k < sentinel && (i == 0 || keys[i - 1] != k)) ? 1 : 0;
-  }
-};
+// The first copies of the distinct valid keys of a sorted array: counted per
+// tile, then (with the tile counts prefix-summed) unpacked to entries. A
+// wavefront takes 1024 consecutive keys of a tile, 64 at a time. (As a scan
+// of flags over all keys and a compaction this took 620 us for 34.6M keys.)
+constexpr int kUniqueTile = 4096;
 
-__global__ void k_compact(const uint64_t* __restrict__ keys, const int64_t* __restrict__ pos,
-                          int64_t m, uint64_t sentinel, int colbits, Ent* __restrict__ ent,
-                          int32_t* __restrict__ major) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  const uint64_t k = keys[i];
-  if (k >= sentinel || (i > 0 && keys[i - 1] == k)) return;
-  const int64_t p = pos[i];
-  ent[p].col = (int32_t)(k & ((1ull << colbits) - 1ull));
-  ent[p].val = 1.0f;
-  major[p] = (int32_t)(k >> colbits);
+__device__ inline bool first_copy(const uint64_t* __restrict__ keys, int64_t i, int64_t m,
+                                  uint64_t sentinel, uint64_t* key) {
+  const uint64_t k = i < m ? keys[i] : sentinel;
+  *key = k;
+  // the key before: the neighbour lane's, except for lane 0
+  uint64_t prev = __shfl_up((unsigned long long)k, 1, 64);
+  if ((threadIdx.x & 63) == 0) prev = i > 0 && i < m ? keys[i - 1] : ~0ull;
+  return k < sentinel && prev != k;
+}
+
+__global__ __launch_bounds__(kThreads) void k_unique_count(const uint64_t* __restrict__ keys,
+                                                           int64_t m, uint64_t sentinel,
+                                                           int64_t* __restrict__ counts) {
+  __shared__ int wcnt[kThreads / 64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t base = (int64_t)blockIdx.x * kUniqueTile + w * (kUniqueTile / 4) + lane;
+  int c = 0;
+#pragma unroll 4
+  for (int j = 0; j < kUniqueTile / kThreads; ++j) {
+    uint64_t k;
+    c += __popcll(__ballot(first_copy(keys, base + j * 64, m, sentinel, &k)));
+  }
+  if (lane == 0) wcnt[w] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) counts[blockIdx.x] = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+}
+
+__global__ __launch_bounds__(kThreads) void k_unique_write(const uint64_t* __restrict__ keys,
+                                                           int64_t m, uint64_t sentinel,
+                                                           int colbits,
+                                                           const int64_t* __restrict__ tile_off,
+                                                           Ent* __restrict__ ent,
+                                                           int32_t* __restrict__ major) {
+  __shared__ int wcnt[kThreads / 64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t base = (int64_t)blockIdx.x * kUniqueTile + w * (kUniqueTile / 4) + lane;
+  constexpr int N = kUniqueTile / kThreads;
+  uint64_t key[N];
+  uint64_t first[N];  // ballots
+  int c = 0;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    first[j] = __ballot(first_copy(keys, base + j * 64, m, sentinel, &key[j]));
+    c += __popcll(first[j]);
+  }
+  if (lane == 0) wcnt[w] = c;
+  __syncthreads();
+  int64_t p = tile_off[blockIdx.x];
+  for (int k = 0; k < w; ++k) p += wcnt[k];
+  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    if ((first[j] >> lane) & 1) {
+      const int64_t q = p + __popcll(first[j] & lt_mask);
+      ent[q].col = (int32_t)(key[j] & ((1ull << colbits) - 1ull));
+      ent[q].val = 1.0f;
+      major[q] = (int32_t)(key[j] >> colbits);
+    }
+    p += __popcll(first[j]);
+  }
 }
 
 // ptr[r] = first position p with major[p] >= r (major is sorted).
@@ -395,6 +440,7 @@ __global__ void k_check_degrees(const int32_t* __restrict__ deg, int64_t n, int*
 
 constexpr int kNormPerThread = 16;
 constexpr int64_t kNormTile = (int64_t)kThreads * kNormPerThread;
+constexpr int kNormRows = 2048;  // rows of a tile whose starts fit the LDS table
 
 // last row r with ptr[r] <= k, searched in [lo, hi]
 __device__ inline int64_t row_of(const int64_t* ptr, int64_t lo, int64_t hi, int64_t k) {
@@ -416,17 +462,48 @@ __global__ __launch_bounds__(kThreads) void k_normalize(const int64_t* __restric
                                                         const int32_t* __restrict__ deg_major,
                                                         const int32_t* __restrict__ deg_minor) {
   __shared__ int64_t r_lo, r_hi;
+  __shared__ int32_t start[kNormRows];  // first entries of the tile's rows, from k0
   const int64_t k0 = (int64_t)blockIdx.x * kNormTile;
   const int64_t k1 = std::min(nnz, k0 + kNormTile) - 1;
   if (threadIdx.x == 0) r_lo = row_of(ptr, 0, n_major - 1, k0);
-  if (threadIdx.x == 1) r_hi = row_of(ptr, 0, n_major - 1, k1);
+  if (threadIdx.x == 64) r_hi = row_of(ptr, 0, n_major - 1, k1);
+  int32_t col[kNormPerThread];
+#pragma unroll
+  for (int j = 0; j < kNormPerThread; ++j) {
+    const int64_t k = k0 + (int64_t)j * kThreads + threadIdx.x;
+    col[j] = ent[k <= k1 ? k : k1].col;
+  }
   __syncthreads();
+  const int64_t lo = r_lo, rows = r_hi - lo + 1;
+  const bool in_lds = rows <= kNormRows;  // else (mostly empty rows) search the row pointer
+  if (in_lds) {
+    for (int i = threadIdx.x; i < rows; i += kThreads) {
+      const int64_t p = ptr[lo + i] - k0;
+      start[i] = p < 0 ? 0 : (int32_t)p;  // the first row may begin before the tile
+    }
+    __syncthreads();
+  }
+#pragma unroll 4
   for (int j = 0; j < kNormPerThread; ++j) {
     const int64_t k = k0 + (int64_t)j * kThreads + threadIdx.x;
     if (k > k1) break;
-    const int64_t r = row_of(ptr, r_lo, r_hi, k);
+    int64_t r;
+    if (in_lds) {
+      const int32_t at = (int32_t)(k - k0);
+      int a = 0, b = (int)rows - 1;  // last row that starts at or before the entry
+      while (a < b) {
+        const int mid = (a + b + 1) >> 1;
+        if (start[mid] <= at)
+          a = mid;
+        else
+          b = mid - 1;
+      }
+      r = lo + a;
+    } else {
+      r = row_of(ptr, lo, r_hi, k);
+    }
     const double dr = (double)deg_major[r] + 1.0;
-    const double dc = (double)deg_minor[ent[k].col] + 1.0;
+    const double dc = (double)deg_minor[col[j]] + 1.0;
     ent[k].val = (float)(1.0 / sqrt(dr * dc));
   }
 }
@@ -488,17 +565,27 @@ gcn_status keys_to_csr(uint64_t** keys, uint64_t** alt, int64_t m, int keybits, 
                        uint64_t sentinel, Mat& mat, int32_t** major, int64_t* nnz_host,
                        int* err_dev, int* err_host, hipStream_t stream) {
   GCN_CHECK(radix_sort_u64(keys, alt, m, keybits, stream));
-  // positions of the distinct keys, written into the spare key buffer
-  int64_t* pos = reinterpret_cast<int64_t*>(*alt);
+  // distinct keys before each tile, in the spare key buffer (m + 1 elements)
+  int64_t* tile_off = reinterpret_cast<int64_t*>(*alt);
+  const int64_t tiles = ceil_div(m, (int64_t)kUniqueTile);
   int64_t* scratch = nullptr;
-  GCN_CHECK(talloc(&scratch, scan_scratch_elems(m), stream, "scan scratch"));
-  gcn_status st = scan_functor(UniqueFlag{*keys, sentinel}, m, pos, scratch, stream);
+  GCN_CHECK(talloc(&scratch, scan_scratch_elems(tiles), stream, "scan scratch"));
+  hipError_t e0 = hipSuccess;
+  if (m > 0) {
+    hipLaunchKernelGGL(k_unique_count, dim3((unsigned)tiles), dim3(kThreads), 0, stream,
+                       (const uint64_t*)*keys, m, sentinel, tile_off);
+    e0 = hipGetLastError();
+  }
+  gcn_status st = e0 != hipSuccess
+                      ? hip_fail(e0, "k_unique_count", __FILE__, __LINE__)
+                      : scan_functor(ArrayInput<int64_t>{tile_off}, tiles, tile_off, scratch, stream);
   tfree(scratch, stream);
   GCN_CHECK(st);
   // one host synchronization: entry count and the id-range flag
   int64_t nnz = 0;
   int errv = 0;
-  hipError_t e1 = hipMemcpyAsync(&nnz, pos + m, sizeof(int64_t), hipMemcpyDeviceToHost, stream);
+  hipError_t e1 = hipMemcpyAsync(&nnz, tile_off + tiles, sizeof(int64_t), hipMemcpyDeviceToHost,
+                                 stream);
   hipError_t e2 = err_dev ? hipMemcpyAsync(&errv, err_dev, sizeof(int), hipMemcpyDeviceToHost,
                                            stream)
                           : hipSuccess;
@@ -513,8 +600,9 @@ gcn_status keys_to_csr(uint64_t** keys, uint64_t** alt, int64_t m, int keybits, 
   GCN_CHECK(alloc_arrays(mat));
   GCN_CHECK(talloc(major, nnz, stream, "entry rows"));
   if (m > 0) {
-    hipLaunchKernelGGL(k_compact, dim3(grid_for(m)), dim3(kThreads), 0, stream, *keys,
-                       (const int64_t*)pos, m, sentinel, colbits, mat.ent, *major);
+    hipLaunchKernelGGL(k_unique_write, dim3((unsigned)tiles), dim3(kThreads), 0, stream,
+                       (const uint64_t*)*keys, m, sentinel, colbits, (const int64_t*)tile_off,
+                       mat.ent, *major);
     GCN_HIP(hipGetLastError());
   }
   hipLaunchKernelGGL(k_row_ptr, dim3(grid_for(mat.n_major + 1)), dim3(kThreads), 0, stream,
