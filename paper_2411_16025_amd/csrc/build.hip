@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <utility>
 
 #include "scan.h"
 
@@ -165,29 +166,33 @@ __device__ inline int row_class(int64_t len, int64_t medium_max) {
   return kChunked;
 }
 
-// Sort key of a row: class in bits [60, 64), then, for the classes of 3 or
-// more entries, decreasing length (kLenMask - min(len, kLenMask)) in bits
-// [32, 60), then the row id. Rows a wavefront takes together then have about
-// the same length, and long rows and full chunks start first.
+// Sort key of a row: the row id in bits [0, 32), above it, for the classes of
+// 3 or more entries, decreasing length (len_cap - min(len, len_cap), a cap of
+// all ones) and above that the class. Rows a wavefront takes together then
+// have about the same length, and long rows and full chunks start first. The
+// order of the rows past the cap does not matter to any kernel; 12 bits of length
+// and 4 of class are two passes of the sort instead of four.
 constexpr uint64_t kLenMask = (1ull << 28) - 1;
 
 __global__ void k_class_keys(const int64_t* __restrict__ ptr, int64_t n_major, int64_t medium_max,
-                             uint64_t* __restrict__ keys) {
+                             uint64_t len_cap, int len_bits, uint64_t* __restrict__ keys) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n_major) return;
   const int64_t len = ptr[r + 1] - ptr[r];
   const int c = row_class(len, medium_max);
-  const uint64_t l = (uint64_t)len < kLenMask ? (uint64_t)len : kLenMask;
-  const uint64_t lcode = c >= kFirstShort + 2 ? kLenMask - l : 0;
-  keys[r] = ((uint64_t)c << 60) | (lcode << 32) | (uint64_t)r;
+  const uint64_t l = (uint64_t)len < len_cap ? (uint64_t)len : len_cap;
+  const uint64_t lcode = c >= kFirstShort + 2 ? len_cap - l : 0;
+  keys[r] = ((uint64_t)c << (32 + len_bits)) | (lcode << 32) | (uint64_t)r;
 }
 
-// per-class row and entry counts and the medium rows over kLongRow entries
-// (integer sums, so the atomics are exact)
-constexpr int kCounts = 2 * kNumClasses + 1;
+// per-class row and entry counts, the medium rows over kLongRow entries, and
+// the chunked rows of at least blocked_min entries and their entries (integer
+// sums, so the atomics are exact)
+constexpr int kCountLong = 2 * kNumClasses, kCountBlocked = kCountLong + 1;
+constexpr int kCounts = kCountBlocked + 2;
 
 __global__ void k_class_count(const int64_t* __restrict__ ptr, int64_t n_major, int64_t medium_max,
-                              unsigned long long* __restrict__ counts) {
+                              int64_t blocked_min, unsigned long long* __restrict__ counts) {
   __shared__ unsigned long long cnt[kCounts];
   if (threadIdx.x < kCounts) cnt[threadIdx.x] = 0;
   __syncthreads();
@@ -197,7 +202,11 @@ __global__ void k_class_count(const int64_t* __restrict__ ptr, int64_t n_major, 
     const int c = row_class(len, medium_max);
     atomicAdd(&cnt[c], 1ull);
     atomicAdd(&cnt[kNumClasses + c], (unsigned long long)len);
-    if (c == kMedium && len > kLongRow) atomicAdd(&cnt[2 * kNumClasses], 1ull);
+    if (c == kMedium && len > kLongRow) atomicAdd(&cnt[kCountLong], 1ull);
+    if (c == kChunked && len >= blocked_min) {
+      atomicAdd(&cnt[kCountBlocked], 1ull);
+      atomicAdd(&cnt[kCountBlocked + 1], (unsigned long long)len);
+    }
   }
   __syncthreads();
   if (threadIdx.x < kCounts && cnt[threadIdx.x])
@@ -263,16 +272,6 @@ __global__ void k_chunks(const int32_t* __restrict__ rows, int64_t n, const int6
 
 // ---- column-blocked pieces of the longest rows ----------------------------------
 
-struct BlockedCount {  // 1 for a row of at least min_len entries
-  const int32_t* rows;
-  const int64_t* ptr;
-  int64_t min_len;
-  __device__ int64_t operator()(int64_t i) const {
-    const int32_t r = rows[i];
-    return ptr[r + 1] - ptr[r] >= min_len ? 1 : 0;
-  }
-};
-
 // bnd[i * (B + 1) + k] = first entry of row rows[i] whose column is at least
 // k * width (k = 0 .. B; the columns of a row increase).
 __global__ void k_block_bounds(const int32_t* __restrict__ rows, int64_t n,
@@ -302,15 +301,6 @@ __global__ void k_block_bounds(const int32_t* __restrict__ rows, int64_t n,
   }
   bnd[t] = lo;
 }
-
-struct RowLength {
-  const int32_t* rows;
-  const int64_t* ptr;
-  __device__ int64_t operator()(int64_t i) const {
-    const int32_t r = rows[i];
-    return ptr[r + 1] - ptr[r];
-  }
-};
 
 // Column blocks merged into one segment of a row of len entries: a row is
 // cut into about len / seg_min segments (a power of two, at most B), each
@@ -384,6 +374,15 @@ __global__ void k_order_pieces(const uint64_t* __restrict__ keys, int64_t n,
   pbeg[t] = tbeg[j];
   plen[t] = tlen[j];
   ppart[t] = (int32_t)(part0 + j);
+}
+
+__global__ void k_totals(const int64_t* __restrict__ a, const int64_t* __restrict__ b,
+                         const int64_t* __restrict__ c, const int64_t* __restrict__ d,
+                         int64_t* __restrict__ out) {
+  const int64_t* p[4] = {a, b, c, d};
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if ((int)threadIdx.x == i) out[i] = p[i] ? *p[i] : 0;
 }
 
 // per-class count of entries whose column is >= halo_from
@@ -683,17 +682,19 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
     GCN_CHECK(slab.alloc(&p.slab, "class rows"));
   }
   GCN_HIP(hipMemsetAsync(counts, 0, kCounts * sizeof(unsigned long long), stream));
+  // the rows of at least blocked_min entries have to come first in their class
+  const int len_bits = std::max(12, bits_for((uint64_t)p.blocked_min));
   hipLaunchKernelGGL(k_class_keys, dim3(grid_for(n)), dim3(kThreads), 0, stream, m.ptr, n,
-                     p.medium_max, keys);
+                     p.medium_max, (1ull << len_bits) - 1, len_bits, keys);
   GCN_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_class_count, dim3(std::min(grid_for(n), 1024u)), dim3(kThreads), 0, stream, m.ptr, n,
-                     p.medium_max, counts);
+                     p.medium_max, p.blocked_min, counts);
   GCN_HIP(hipGetLastError());
-  // four stable 8-bit passes over bits [32, 64): by length code, then by class
-  GCN_CHECK(radix_pass_u64(keys, sorted, n, 32, stream));
-  GCN_CHECK(radix_pass_u64(sorted, keys, n, 40, stream));
-  GCN_CHECK(radix_pass_u64(keys, sorted, n, 48, stream));
-  GCN_CHECK(radix_pass_u64(sorted, keys, n, 56, stream));
+  // stable 8-bit passes from bit 32: by length code, then by class
+  for (int shift = 32; shift < 32 + len_bits + 4; shift += 8) {
+    GCN_CHECK(radix_pass_u64(keys, sorted, n, shift, stream));
+    std::swap(keys, sorted);
+  }
   hipLaunchKernelGGL(k_low32, dim3(grid_for(n)), dim3(kThreads), 0, stream,
                      (const uint64_t*)keys, n, p.rows);
   GCN_HIP(hipGetLastError());
@@ -705,7 +706,7 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
     p.class_off[c + 1] = p.class_off[c] + (int64_t)host_counts[c];
     p.class_nnz[c] = (int64_t)host_counts[kNumClasses + c];
   }
-  p.n_long = (int64_t)host_counts[2 * kNumClasses];
+  p.n_long = (int64_t)host_counts[kCountLong];
   // rows up to the medium class read their start and length from here (one
   // load fewer in their chain of dependent loads)
   const int64_t n_rowk = p.class_off[kMedium + 1] - p.class_off[kFirstShort];
@@ -729,19 +730,15 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
   int64_t* scratch = nullptr;
   GCN_CHECK(tmp.alloc(&scratch, scan_scratch_elems(nc_rows), "scan scratch"));
   if (blocking) {
-    int64_t* flag_off = nullptr;
-    GCN_CHECK(tmp.alloc(&flag_off, nc_rows + 1, "blocked-row scan"));
-    GCN_CHECK(scan_functor(BlockedCount{crow, m.ptr, p.blocked_min}, nc_rows, flag_off, scratch,
-                           stream));
-    GCN_HIP(hipMemcpyAsync(&p.n_blocked, flag_off + nc_rows, 8, hipMemcpyDeviceToHost, stream));
-    GCN_HIP(hipStreamSynchronize(stream));
+    p.n_blocked = (int64_t)host_counts[kCountBlocked];
+    p.blocked_nnz = (int64_t)host_counts[kCountBlocked + 1];
   }
   const int64_t nb = p.n_blocked;
   const int32_t* chrow = crow + nb;  // rows of the chunk table
   const int64_t nch = nc_rows - nb;
   int64_t *chunk_off = nullptr, *part_off = nullptr, *giant_idx = nullptr;
-  int64_t *bnd = nullptr, *piece_off = nullptr, *pscratch = nullptr, *len_off = nullptr;
-  int64_t tot[5] = {0, 0, 0, 0, 0};
+  int64_t *bnd = nullptr, *piece_off = nullptr, *pscratch = nullptr;
+  int64_t tot[4] = {0, 0, 0, 0};
   if (nch > 0) {
     GCN_CHECK(tmp.alloc(&chunk_off, nch + 1, "chunk offsets"));
     GCN_CHECK(tmp.alloc(&part_off, nch + 1, "partial offsets"));
@@ -752,9 +749,6 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
                            stream));
     GCN_CHECK(scan_functor(ChunkCount{chrow, m.ptr, p.chunk_len, 2}, nch, giant_idx, scratch,
                            stream));
-    GCN_HIP(hipMemcpyAsync(&tot[0], chunk_off + nch, 8, hipMemcpyDeviceToHost, stream));
-    GCN_HIP(hipMemcpyAsync(&tot[1], part_off + nch, 8, hipMemcpyDeviceToHost, stream));
-    GCN_HIP(hipMemcpyAsync(&tot[2], giant_idx + nch, 8, hipMemcpyDeviceToHost, stream));
   }
   if (nb > 0) {
     GCN_CHECK(tmp.alloc(&bnd, nb * (B + 1), "block bounds"));
@@ -765,17 +759,21 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
     GCN_HIP(hipGetLastError());
     GCN_CHECK(scan_functor(PieceCount{bnd, B, p.piece_max, p.seg_min}, nb * B, piece_off, pscratch,
                            stream));
-    GCN_HIP(hipMemcpyAsync(&tot[3], piece_off + nb * B, 8, hipMemcpyDeviceToHost, stream));
-    // entries of the blocked rows
-    GCN_CHECK(tmp.alloc(&len_off, nb + 1, "blocked entry scan"));
-    GCN_CHECK(scan_functor(RowLength{crow, m.ptr}, nb, len_off, pscratch, stream));
-    GCN_HIP(hipMemcpyAsync(&tot[4], len_off + nb, 8, hipMemcpyDeviceToHost, stream));
   }
+  // the totals in one copy
+  int64_t* dtot = nullptr;
+  GCN_CHECK(tmp.alloc(&dtot, 4, "plan totals"));
+  hipLaunchKernelGGL(k_totals, dim3(1), dim3(64), 0, stream,
+                     nch > 0 ? (const int64_t*)(chunk_off + nch) : nullptr,
+                     nch > 0 ? (const int64_t*)(part_off + nch) : nullptr,
+                     nch > 0 ? (const int64_t*)(giant_idx + nch) : nullptr,
+                     nb > 0 ? (const int64_t*)(piece_off + nb * B) : nullptr, dtot);
+  GCN_HIP(hipGetLastError());
+  GCN_HIP(hipMemcpyAsync(tot, dtot, sizeof(tot), hipMemcpyDeviceToHost, stream));
   GCN_HIP(hipStreamSynchronize(stream));
   p.n_chunks = tot[0];
   const int64_t n_cparts = tot[1], n_cgiant = tot[2];
   p.n_pieces = tot[3];
-  p.blocked_nnz = tot[4];
   p.n_parts = n_cparts + p.n_pieces;
   p.n_giant = n_cgiant + nb;
   if (p.n_parts >= (1ll << 31)) {
@@ -820,12 +818,13 @@ gcn_status build_plan(Mat& m, hipStream_t stream) {
                        n_cparts, tbeg, tlen, keys, p.giant_row + n_cgiant,
                        p.giant_part_off + n_cgiant);
     GCN_HIP(hipGetLastError());
-    // stable passes over bits [32, 56): decreasing length, then block
-    GCN_CHECK(radix_pass_u64(keys, alt, p.n_pieces, 32, stream));
-    GCN_CHECK(radix_pass_u64(alt, keys, p.n_pieces, 40, stream));
-    GCN_CHECK(radix_pass_u64(keys, alt, p.n_pieces, 48, stream));
+    // stable passes from bit 32: decreasing length (9 bits), then block
+    for (int shift = 32; shift < 41 + bits_for((uint64_t)(B - 1)); shift += 8) {
+      GCN_CHECK(radix_pass_u64(keys, alt, p.n_pieces, shift, stream));
+      std::swap(keys, alt);
+    }
     hipLaunchKernelGGL(k_order_pieces, dim3(grid_for(p.n_pieces)), dim3(kThreads), 0, stream,
-                       (const uint64_t*)alt, p.n_pieces, (const int64_t*)tbeg,
+                       (const uint64_t*)keys, p.n_pieces, (const int64_t*)tbeg,
                        (const int32_t*)tlen, n_cparts, p.piece_beg, p.piece_len, p.piece_part);
     GCN_HIP(hipGetLastError());
   }
