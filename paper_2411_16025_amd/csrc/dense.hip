@@ -1585,11 +1585,14 @@ bool resident_fits(int64_t M, int64_t N, int64_t K, bool masked) {
   return ceil_div(K, (int64_t)16) * 16 * 48 * (int64_t)sizeof(float) <= kResMaxLds;
 }
 
+constexpr int64_t kFewTiles = 512;
+
 template <int OP>
 hipError_t launch_tall(int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
                  int64_t ldb, float* C, int64_t ldc, const float* mask, int64_t ldm,
                  bool relu, hipStream_t stream) {
-  const int bn = tile_n(N);
+  int bn = tile_n(N);
+  if (bn == 128 && ceil_div(M, (int64_t)kTile) * ceil_div(N, (int64_t)bn) < kFewTiles) bn = 64;
   // staged 16-byte stores need 16-byte aligned rows of C (and of the mask)
   const bool cvec = aligned16(C, ldc) && (!mask || aligned16(mask, ldm));
   // ring: D slots of CPS chunks (D * CPS must divide the chunk count)
@@ -1605,7 +1608,12 @@ hipError_t launch_tall(int64_t M, int64_t N, int64_t K, const float* A, int64_t 
   }
 #undef GCN_BRES
   const dim3 grid((unsigned)ceil_div(M, kTile), (unsigned)ceil_div(N, bn));
-  if (bn == 48) {  // two 16-row blocks per wavefront (each B fragment feeds two MFMAs)
+  // few tiles: smaller ones, so that more CUs share the products
+  const bool few = ceil_div(M, (int64_t)kTile) * ceil_div(N, (int64_t)bn) < kFewTiles;
+  if (bn == 48 && few) {
+    hipLaunchKernelGGL((k_gemm_tall_v<OP, 48, 1>), grid, dim3(kThreads), 0, stream, M, N, K, A,
+                       lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
+  } else if (bn == 48) {  // two 16-row blocks per wavefront (each B fragment feeds two MFMAs)
     const dim3 grid2((unsigned)ceil_div(M, (int64_t)kTile * 2), (unsigned)ceil_div(N, bn));
     hipLaunchKernelGGL((k_gemm_tall_v<OP, 48, 2>), grid2, dim3(kThreads), 0, stream, M, N, K, A,
                        lda, B, ldb, C, ldc, mask, ldm, relu, cvec);
