@@ -36,80 +36,79 @@ constexpr int kThreadsS = 256;
 
 inline int64_t round4(int64_t v) { return (v + 3) & ~int64_t(3); }
 
-// Columns of C below K that no kernel of the layer writes: [f, zo),
-// [zo + zw, oc) (zw: the width of the middle block's data), the ones column
-// oc and (oc, K).
-__global__ __launch_bounds__(kThreadsS) void k_concat_tail(int64_t n, int64_t f, int64_t zo,
-                                                           int64_t zw, int64_t oc, int64_t K,
-                                                           float* __restrict__ c, int64_t ldc) {
-  const int64_t a = zo - f, b = oc - zo - zw;  // the two padding runs
-  const int64_t per_row = K - f - zw;
-  const int64_t t = (int64_t)blockIdx.x * kThreadsS + threadIdx.x;
-  if (t >= n * per_row) return;
-  const int64_t i = t / per_row, k = t % per_row;
-  int64_t col;
-  if (k < a)
-    col = f + k;
-  else if (k < a + b)
-    col = zo + zw + (k - a);
-  else
-    col = oc + (k - a - b);
-  c[i * ldc + col] = (col == oc) ? 1.f : 0.f;
-}
+// What a layer's buffers hold before its kernels run, one element per thread:
+//  * the columns of C below K that no kernel writes: [f, zo), [zo + zw, oc) and
+//    [oc, K), 0 but for the ones column oc;
+//  * Wp [K x fop]: rows [0, f) = W_self, [zo, zo + f) = W_neigh (or, when the
+//    layer aggregates Y W_neigh, [zo, zo + fo) = the identity), row oc = b,
+//    every other entry 0 (fo columns used of fop);
+//  * for a layer that aggregates Y W_neigh, W_neigh padded to [f x fop], and
+//    B [f x 2 fop] = [W_self | 0 | W_neigh | 0] (the weights of its input
+//    gradient: dY = [dO | G] B^T).
+// All layers in one launch (eight launches for three layers were 36 us of a
+// step of 5,000 nodes): ranges of whole workgroups, first[i] .. first[i + 1].
+struct SetupLayer {
+  int64_t f, zo, zw, oc, K, ldc, fo, fop;
+  bool ident;
+  const float *ws, *wn_in, *b;
+  float *c, *wp, *wn, *bc;
+};
 
-// Wp [K x fop]: rows [0, f) = W_self, [zo, zo + f) = W_neigh (or, when the
-// layer aggregates Y W_neigh, [zo, zo + fo) = the identity), row oc = b,
-// every other entry 0 (fo columns used of fop).
-__global__ __launch_bounds__(kThreadsS) void k_pack_weights(int64_t f, int64_t zo, int64_t oc,
-                                                            int64_t K, int64_t fo, int64_t fop,
-                                                            bool ident,
-                                                            const float* __restrict__ ws,
-                                                            const float* __restrict__ wn,
-                                                            const float* __restrict__ b,
-                                                            float* __restrict__ wp) {
-  const int64_t t = (int64_t)blockIdx.x * kThreadsS + threadIdx.x;
-  if (t >= K * fop) return;
-  const int64_t r = t / fop, c = t % fop;
-  float v = 0.f;
-  if (c < fo) {
-    if (r < f)
-      v = ws[r * fo + c];
-    else if (ident && r >= zo && r < zo + fo)
-      v = r - zo == c ? 1.f : 0.f;
-    else if (!ident && r >= zo && r < zo + f)
-      v = wn[(r - zo) * fo + c];
-    else if (r == oc)
-      v = b[c];
+struct SetupArgs {
+  int64_t n;
+  SetupLayer L[3];
+  int64_t first[13];  // workgroups: per layer C, Wp, W_neigh, B
+};
+
+__global__ __launch_bounds__(kThreadsS) void k_setup(SetupArgs a) {
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < 12; ++i)
+    if ((int64_t)blockIdx.x >= a.first[i]) k = i;
+  const SetupLayer& y = a.L[k >> 2];
+  const int64_t t = ((int64_t)blockIdx.x - a.first[k]) * kThreadsS + threadIdx.x;
+  if ((k & 3) == 0) {
+    const int64_t r1 = y.zo - y.f, r2 = y.oc - y.zo - y.zw;  // the two padding runs
+    const int64_t per_row = y.K - y.f - y.zw;
+    if (t >= a.n * per_row) return;
+    const int64_t i = t / per_row, j = t % per_row;
+    int64_t col;
+    if (j < r1)
+      col = y.f + j;
+    else if (j < r1 + r2)
+      col = y.zo + y.zw + (j - r1);
+    else
+      col = y.oc + (j - r1 - r2);
+    y.c[i * y.ldc + col] = (col == y.oc) ? 1.f : 0.f;
+  } else if ((k & 3) == 1) {
+    if (t >= y.K * y.fop) return;
+    const int64_t r = t / y.fop, c = t % y.fop;
+    float v = 0.f;
+    if (c < y.fo) {
+      if (r < y.f)
+        v = y.ws[r * y.fo + c];
+      else if (y.ident && r >= y.zo && r < y.zo + y.fo)
+        v = r - y.zo == c ? 1.f : 0.f;
+      else if (!y.ident && r >= y.zo && r < y.zo + y.f)
+        v = y.wn_in[(r - y.zo) * y.fo + c];
+      else if (r == y.oc)
+        v = y.b[c];
+    }
+    y.wp[t] = v;
+  } else if ((k & 3) == 2) {
+    if (t >= y.f * y.fop) return;
+    const int64_t r = t / y.fop, c = t % y.fop;
+    y.wn[t] = c < y.fo ? y.wn_in[r * y.fo + c] : 0.f;
+  } else {
+    if (t >= y.f * 2 * y.fop) return;
+    const int64_t r = t / (2 * y.fop), c = t % (2 * y.fop);
+    float v = 0.f;
+    if (c < y.fo)
+      v = y.ws[r * y.fo + c];
+    else if (c >= y.fop && c < y.fop + y.fo)
+      v = y.wn_in[r * y.fo + c - y.fop];
+    y.bc[t] = v;
   }
-  wp[t] = v;
-}
-
-// dst [rows x ldd] = src [rows x cols] (ld lds) in the first cols columns,
-// 0 in the columns [cols, ldd).
-__global__ __launch_bounds__(kThreadsS) void k_pad_cols(int64_t rows, int64_t cols,
-                                                        const float* __restrict__ src, int64_t lds,
-                                                        float* __restrict__ dst, int64_t ldd) {
-  const int64_t t = (int64_t)blockIdx.x * kThreadsS + threadIdx.x;
-  if (t >= rows * ldd) return;
-  const int64_t r = t / ldd, c = t % ldd;
-  dst[t] = c < cols ? src[r * lds + c] : 0.f;
-}
-
-// B [f x 2 fop] = [W_self | 0 | W_neigh | 0] (the weights of the input
-// gradient of a layer that aggregates Y W_neigh: dY = [dO | G] B^T).
-__global__ __launch_bounds__(kThreadsS) void k_pack_bcat(int64_t f, int64_t fo, int64_t fop,
-                                                         const float* __restrict__ ws,
-                                                         const float* __restrict__ wn,
-                                                         float* __restrict__ bc) {
-  const int64_t t = (int64_t)blockIdx.x * kThreadsS + threadIdx.x;
-  if (t >= f * 2 * fop) return;
-  const int64_t r = t / (2 * fop), c = t % (2 * fop);
-  float v = 0.f;
-  if (c < fo)
-    v = ws[r * fo + c];
-  else if (c >= fop && c < fop + fo)
-    v = wn[r * fo + c - fop];
-  bc[t] = v;
 }
 
 // Zero the padding columns [fo, fop) and [fop + fo, 2 fop) of DG [n x 2 fop]
@@ -422,25 +421,24 @@ gcn_status sage_forward(const gcn_graph* g, const float* X, int64_t ldx, int64_t
   if (st == GCN_OK && lp_mask) st = talloc(&m.xp, n * L[0].fp, s, "input with label embeddings");
   GCN_CHECK(st);
   // packed weights and the constant columns of each C
+  SetupArgs sa{};
+  sa.n = n;
+  int64_t nb = 0;
   for (int l = 0; l < 3; ++l) {
-    Layer& y = L[l];
-    hipLaunchKernelGGL(k_pack_weights, dim3(blocks(y.K * y.fop)), dim3(kThreadsS), 0, s, y.f,
-                       y.zo, y.oc, y.K, y.fo, y.fop, y.tf, params[3 * l], params[3 * l + 1],
-                       params[3 * l + 2], y.wp);
-    GCN_HIP(hipGetLastError());
+    const Layer& y = L[l];
     const int64_t zw = y.tf ? y.fo : y.f;  // columns of the middle block the layer writes
-    hipLaunchKernelGGL(k_concat_tail, dim3(blocks(n * (y.K - y.f - zw))), dim3(kThreadsS), 0, s, n,
-                       y.f, y.zo, zw, y.oc, y.K, y.c, y.ldc);
-    GCN_HIP(hipGetLastError());
-    if (y.tf) {
-      hipLaunchKernelGGL(k_pad_cols, dim3(blocks(y.f * y.fop)), dim3(kThreadsS), 0, s, y.f, y.fo,
-                         params[3 * l + 1], y.fo, y.wn, y.fop);
-      GCN_HIP(hipGetLastError());
-      hipLaunchKernelGGL(k_pack_bcat, dim3(blocks(y.f * 2 * y.fop)), dim3(kThreadsS), 0, s, y.f,
-                         y.fo, y.fop, params[3 * l], params[3 * l + 1], y.bc);
-      GCN_HIP(hipGetLastError());
+    sa.L[l] = {y.f, y.zo, zw, y.oc, y.K, y.ldc, y.fo, y.fop, y.tf, params[3 * l],
+               params[3 * l + 1], params[3 * l + 2], y.c, y.wp, y.wn, y.bc};
+    const int64_t work[4] = {n * (y.K - y.f - zw), y.K * y.fop, y.tf ? y.f * y.fop : 0,
+                             y.tf ? y.f * 2 * y.fop : 0};
+    for (int k = 0; k < 4; ++k) {
+      sa.first[4 * l + k] = nb;
+      nb += ceil_div(work[k], (int64_t)kThreadsS);
     }
   }
+  sa.first[12] = nb;
+  hipLaunchKernelGGL(k_setup, dim3((unsigned)nb), dim3(kThreadsS), 0, s, sa);
+  GCN_HIP(hipGetLastError());
   const float* h = X;
   int64_t ldh = ldx;
   if (lp_mask) {
