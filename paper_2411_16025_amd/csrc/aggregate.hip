@@ -671,8 +671,10 @@ __global__ __launch_bounds__(64 * kRowsWaves, GCN_MIN_WAVES) void k_rows(RowsArg
 }
 
 // The same for a matrix of so few rows that wavefronts for each are all in
-// flight at once (up to 4,096 rows and feature tiles: 16 wavefronts per CU): time is then the longest chain of dependent loads, so a row
-// takes a whole wavefront (kSmallUnroll gathers in flight per lane) and a chunk kSmallWaves of them.
+// flight at once (up to 4,096 rows and feature tiles: 16 wavefronts per CU):
+// time is then the longest chain of dependent loads, so a row takes a whole
+// wavefront (kSmallUnroll gathers in flight per lane) and a chunk kSmallWaves
+// of them.
 constexpr int kSmallWaves = 8;
 constexpr int kSmallUnroll = 8;
 
@@ -821,10 +823,11 @@ gcn_status launch_all(const Mat& m, const Src& src, float* y, int64_t ldy, int F
   // 170,003 x 47: 111 -> 66; 65,536 x 256, 6.7e8 features gathered: 191 -> 161).
   // From about 8e8 on each class fills the chip by itself, and together they
   // disturb each other's rows in the caches (170,003 x 256, 48 a row: 540 ->
-  // 590). Graphs without long rows have neither chain nor launches to save
-  // (uniform, 33 a row, 32,768 x 256: 118 -> 122) unless all their rows are in
-  // flight at once (4,096 x 64: the kernel 9 -> 4).
-  const bool long_rows = p.n_chunks > 0 || p.n_long > 0;
+  // 590). Graphs without rows past the medium class, or with hardly any others,
+  // have neither chain nor launches to save (uniform, 33 a row, 32,768 x 256:
+  // 118 -> 122; 50 a row, 31,583 x 224 in bf16: 75 -> 83) unless all their rows
+  // are in flight at once (4,096 x 64: the kernel 9 -> 4).
+  const bool long_rows = p.n_chunks > 0 && p.n_chunks < m.n_major / 4;
   const bool all_in_flight = m.n_major * tiles <= 4096;
   if (p.n_pieces == 0 && m.nnz <= kFusedGathers / F && (long_rows || all_in_flight)) {
     RowsArgs a{};
