@@ -158,6 +158,8 @@ gcn_status talloc(T** p, int64_t count, hipStream_t stream, const char* what) {
                  what);
 }
 void tfree(void* p, hipStream_t stream);
+// Whether work on the stream is being recorded (or the runtime cannot tell).
+bool stream_capturing(hipStream_t stream);
 // One per entry point that takes temporaries, from its start to its end (see
 // runtime.hip); calls without one are ordered block by block.
 struct CallScope {

@@ -177,14 +177,15 @@ __device__ inline f4 load4(const float* __restrict__ p, int64_t row, int64_t row
 }
 
 // Wide-tile C = A op(B) for 16-byte aligned operands: a 64 x BN tile per
-// 256-thread workgroup (BN up to 256, so the tall operand is read once per
+// 256-thread workgroup (BN up to 128, so the tall operand is read once per
 // BN columns), 32-deep K slices in LDS, software-pipelined: the next slice's
 // A and B tiles are loaded into registers while the current slice is
 // multiplied from LDS, so the loads' latency overlaps the matrix-core work.
 // B is kept k-major for NN and n-major for NT (both written with 16-byte
 // LDS stores). With mask, C = 0 where mask <= 0 (a ReLU backward); with
 // relu, C = max(C, 0) (a ReLU forward).
-// Workgroups per CU the tiles must fit (fewer registers, more waves to overlap LDS and global latency).
+// Workgroups per CU the tiles must fit (fewer registers, more waves to overlap
+// LDS and global latency).
 #ifndef GCN_GEMM_MIN_BLOCKS
 #define GCN_GEMM_MIN_BLOCKS 4
 #endif
@@ -1743,11 +1744,17 @@ gcn_status gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int
   // 30,000 x 128 x 256 28 -> 22; 3,000 x 128 x 256 19.6 -> 19.5, x 100 x 64 8.4 ->
   // 12.2), and every unaligned one that is not tiny (the general kernel loads
   // element by element: 500,000 x 47 x 256 418 us, 170). Narrower aligned
-  // outputs are bound by reading A either way.
+  // outputs are bound by reading A either way. The packed B is the only scratch
+  // of these products: a call being captured, and one that finds no memory for
+  // it, take the kernels that need none.
   const bool outweighs = M * N * K >= kSplitMinWork || (N > 128 && K >= 96 && M >= 256);
   if ((vec ? N > 64 && outweighs : M >= kSplitMinRows) &&
-      gemm_split_tall_takes(M, N, K, lda, ldc, mask ? ldm : 0))
-    return gemm_split_tall(op, M, N, K, A, lda, B, ldb, C, ldc, mask, ldm, relu, stream);
+      gemm_split_tall_takes(M, N, K, lda, ldc, mask ? ldm : 0) && !stream_capturing(stream)) {
+    const gcn_status st =
+        gemm_split_tall(op, M, N, K, A, lda, B, ldb, C, ldc, mask, ldm, relu, stream);
+    if (st != GCN_ENOMEM) return st;
+    clear_error();
+  }
   const dim3 grid((unsigned)ceil_div(M, kTile), (unsigned)ceil_div(N, kTile));
   ProfScope ps(op == GCN_GEMM_NN ? "gemm_nn" : "gemm_nt", stream);
   if (vec && op == GCN_GEMM_NN)

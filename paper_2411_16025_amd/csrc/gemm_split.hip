@@ -524,6 +524,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
 bool gemm_split_tall_takes(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldc,
                            int64_t ldm) {
   return M < (int64_t(1) << 33) && N < (int64_t(1) << 30) && K >= 16 && K <= 4096 &&
+         N * K < (int64_t(1) << 34) &&  // a thread per 8 elements of the packed B
          lda < (int64_t(1) << 22) && ldc < (int64_t(1) << 27) && ldm < (int64_t(1) << 27);
 }
 

@@ -159,13 +159,22 @@ bool may_keep(hipStream_t stream, int* dev) {
   if (hipGetDevice(dev) != hipSuccess || *dev < 0 || *dev >= 64) return false;
   if (!stream) return true;
   if (stream == hipStreamPerThread || stream == hipStreamLegacy) return false;
+  return !stream_capturing(stream);
+}
+
+}  // namespace
+
+bool stream_capturing(hipStream_t stream) {
+  if (!stream || stream == hipStreamLegacy) return false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
     (void)hipGetLastError();
-    return false;
+    return true;
   }
-  return cs == hipStreamCaptureStatusNone;
+  return cs != hipStreamCaptureStatusNone;
 }
+
+namespace {
 
 bool callers_stream(int dev, hipStream_t stream) { return stream && stream != g_side[dev]; }
 

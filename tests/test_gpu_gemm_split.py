@@ -114,3 +114,37 @@ def test_not_finite(G, op):
     fin = np.isfinite(want)
     scale = np.nan_to_num(np.abs(A), nan=0, posinf=0).astype(np.float64) @ np.abs(B).astype(np.float64)
     assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-5 * scale[fin])
+
+
+@pytest.mark.parametrize("op,M,N,K", [("NN", 4097, 47, 100), ("NN", 8192, 256, 100),
+                                      ("NT", 4100, 161, 47)])
+def test_captured(G, op, M, N, K):
+    """Captured products record kernels only (no allocation), and every replay
+    multiplies what the operands hold then."""
+    import torch
+    note("split captured %s %s" % (op, (M, N, K)))
+    code = G.GCN_GEMM_NN if op == "NN" else G.GCN_GEMM_NT
+    Ad, Bd = torch.empty((M, K), device="cuda:0"), torch.empty(
+        (K, N) if op == "NN" else (N, K), device="cuda:0")
+    Cd = torch.empty((M, N), device="cuda:0")
+    Ad.fill_(1.0)
+    Bd.fill_(1.0)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()  # default priority
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        G.gcn_gemm_f32(code, Ad, Bd, C=Cd)
+    torch.cuda.synchronize()
+    for rep in range(3):
+        A, B = synth.uniform(310 + rep, M, K), synth.uniform(320 + rep, K, N)
+        Ad.copy_(dev(A))
+        Bd.copy_(dev(B if op == "NN" else np.ascontiguousarray(B.T)))
+        Cd.fill_(7.0)  # eager work between the replays
+        eager = host(G.gcn_gemm_f32(code, Ad, Bd))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want, scale = _pair(A, B)
+        assert_close(host(Cd), want, scale, what="replay %d" % rep)
+        assert_close(eager, want, scale, what="eager %d" % rep)
