@@ -444,7 +444,9 @@ def run_gemm(args):
     multiple of 4 floats), timed with HIP events on the stream the library
     launches on. Per product: the algorithmic bytes (each operand and the
     result once) and flops, the roofline time max(flops / 157.3 TFLOP/s,
-    bytes / 8 TB/s), and its fraction of the measured time."""
+    bytes / 8 TB/s), and its fraction of the measured time. The flops are
+    priced at the fp32 matrix-core peak; the large products run as six bf16
+    ones over exact three-way splits, so their fraction may exceed 1."""
     import torch
     import synth
     import paper_2411_16025_amd as G
