@@ -8,6 +8,7 @@
 #include <string>
 
 #include "../../include/gcnagg.h"
+#include "workspace.h"
 
 namespace gcn {
 
@@ -122,12 +123,6 @@ gcn_status hip_fail(hipError_t e, const char* what, const char* file, int line);
     if (s_ != GCN_OK) return s_;               \
   } while (0)
 
-gcn_status dmalloc(void** p, size_t bytes, const char* what);
-template <class T>
-gcn_status dalloc(T** p, int64_t count, const char* what) {
-  return dmalloc(reinterpret_cast<void**>(p), (size_t)(count > 0 ? count : 1) * sizeof(T), what);
-}
-void dfree(void* p);
 // Several arrays in one allocation (hipMalloc and hipFree cost about 60 and
 // 150 us each): add() the arrays, then alloc() sets their pointers.
 struct Slab {
@@ -149,33 +144,6 @@ struct Slab {
     return GCN_OK;
   }
 };
-// Temporaries of the work enqueued on `stream`, kept for later calls on it
-// (runtime.hip).
-gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what);
-template <class T>
-gcn_status talloc(T** p, int64_t count, hipStream_t stream, const char* what) {
-  return tmalloc(reinterpret_cast<void**>(p), (size_t)(count > 0 ? count : 1) * sizeof(T), stream,
-                 what);
-}
-void tfree(void* p, hipStream_t stream);
-// Whether work on the stream is being recorded (or the runtime cannot tell).
-bool stream_capturing(hipStream_t stream);
-// One per entry point that takes temporaries, from its start to its end (see
-// runtime.hip); calls without one are ordered block by block.
-struct CallScope {
-  hipStream_t stream;
-  CallScope* outer;
-  int dev = 0;
-  bool waited = false, released = false;
-  explicit CallScope(void* stream);
-  CallScope(const CallScope&) = delete;
-  CallScope& operator=(const CallScope&) = delete;
-  ~CallScope();
-};
-// Graphs alive per device (idle temporaries are given back with the last one).
-void graph_opened(int dev);
-void graph_closed(int dev);
-
 // Work that may overlap the caller's stream runs on a second stream of the
 // current device (non-blocking, default priority, created on first use and
 // kept until the process ends). fork() makes the side stream wait for all
@@ -191,6 +159,9 @@ struct SideWork {
   gcn_status join();
   ~SideWork();
 };
+
+// The side stream of a device (null until its first use).
+hipStream_t side_stream(int dev);
 
 // Stream-ordered temporaries released when the scope ends, on every return
 // path (error returns included).

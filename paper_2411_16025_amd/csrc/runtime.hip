@@ -1,15 +1,11 @@
-// Error reporting, device allocation helpers and per-kernel event profiling.
+// Error reporting, the side stream and per-kernel event profiling.
 
 #include <atomic>
 #include <cstdarg>
 #include <deque>
-#include <iterator>
-#include <list>
 #include <map>
 #include <mutex>
 #include <string>
-#include <unordered_map>
-#include <utility>
 #include <vector>
 
 #include "common.h"
@@ -51,27 +47,12 @@ gcn_status hip_fail(hipError_t e, const char* what, const char* file, int line) 
   return (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) ? GCN_ENOMEM : GCN_EHIP;
 }
 
-gcn_status dmalloc(void** p, size_t bytes, const char* what) {
-  *p = nullptr;
-  hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess) {
-    *p = nullptr;
-    (void)hipGetLastError();
-    set_error("device allocation of %zu bytes for %s failed: %s", bytes, what,
-              hipGetErrorString(e));
-    return GCN_ENOMEM;
-  }
-  return GCN_OK;
-}
-
-void dfree(void* p) {
-  if (p) (void)hipFree(p);
-}
-
 namespace {
 std::mutex g_side_mu;
 std::atomic<hipStream_t> g_side[64] = {};  // set once per device, under g_side_mu
 }  // namespace
+
+hipStream_t side_stream(int dev) { return g_side[dev]; }
 
 gcn_status SideWork::init(hipStream_t m) {
   main = m;
@@ -113,225 +94,6 @@ SideWork::~SideWork() {
   (void)join();
   if (ev_fork) (void)hipEventDestroy(ev_fork);
   if (ev_join) (void)hipEventDestroy(ev_join);
-}
-
-// Temporaries. hipFreeAsync waits for the work enqueued on its stream (20
-// buffers of 64 MiB written by 20 kernels: 698 us with hipMallocAsync and
-// hipFreeAsync around them, 363 us with kept buffers), so a call that released
-// its temporaries with it ran in step with the host. Released blocks are
-// kept here instead, per device and stream: the next call on that stream takes
-// them without waiting, since its work is ordered behind the work that used them.
-//  * A caller's stream may be destroyed with its work pending and a new one
-//    created at its address. So a call that released blocks ends with an event
-//    on its stream, and the first block taken by a later call at that address
-//    waits for it: nothing to wait for on the stream itself, and a real
-//    dependency on another. The NULL stream and the library's own are not
-//    destroyed and need no event.
-//  * A block goes to another stream only through the driver.
-//  * While a stream is being captured, its temporaries are nodes of the graph
-//    (hipMallocAsync / hipFreeAsync), as a graph may be replayed on any stream.
-//  * At most a quarter of the device's memory is kept idle, the oldest blocks
-//    going first; all of it is given back when an allocation fails, and all
-//    but kKeepIdle when the last graph on the device is freed.
-namespace {
-
-struct Block {
-  void* ptr;
-  size_t bytes;
-  int dev;
-  hipStream_t stream;
-};
-
-std::mutex g_cache_mu;
-std::list<Block> g_idle;                  // oldest first
-std::unordered_map<void*, Block> g_live;  // handed out
-std::map<std::pair<int, hipStream_t>, hipEvent_t> g_last_use;  // callers' streams
-size_t g_idle_bytes[64] = {};
-size_t g_idle_max[64] = {};
-int g_graphs[64] = {};
-constexpr size_t kKeepIdle = size_t(256) << 20;
-
-thread_local CallScope* t_scope = nullptr;
-
-// The current device; false where blocks cannot be kept (a capturing stream,
-// the special handles, a stream the runtime refuses).
-bool may_keep(hipStream_t stream, int* dev) {
-  if (hipGetDevice(dev) != hipSuccess || *dev < 0 || *dev >= 64) return false;
-  if (!stream) return true;
-  if (stream == hipStreamPerThread || stream == hipStreamLegacy) return false;
-  return !stream_capturing(stream);
-}
-
-}  // namespace
-
-bool stream_capturing(hipStream_t stream) {
-  if (!stream || stream == hipStreamLegacy) return false;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
-    (void)hipGetLastError();
-    return true;
-  }
-  return cs != hipStreamCaptureStatusNone;
-}
-
-namespace {
-
-bool callers_stream(int dev, hipStream_t stream) { return stream && stream != g_side[dev]; }
-
-// Give a block back (the caller holds no lock). Where the stream is the
-// caller's own, it orders the release; otherwise hipFree waits for the device.
-void give_back(const Block& b, hipStream_t stream) {
-  if (!stream && !b.stream)
-    (void)hipFreeAsync(b.ptr, stream);
-  else
-    (void)hipFree(b.ptr);
-}
-
-// Idle blocks of a device, oldest first, until at most keep bytes are left.
-std::list<Block> take_idle(int dev, size_t keep) {
-  std::list<Block> out;
-  std::lock_guard<std::mutex> lk(g_cache_mu);
-  for (auto it = g_idle.begin(); it != g_idle.end() && g_idle_bytes[dev] > keep;) {
-    auto next = std::next(it);
-    if (it->dev == dev) {
-      g_idle_bytes[dev] -= it->bytes;
-      out.splice(out.end(), g_idle, it);
-    }
-    it = next;
-  }
-  return out;
-}
-
-// The event that ends the last call on a caller's stream that released blocks.
-void mark_last_use(int dev, hipStream_t stream) {
-  std::lock_guard<std::mutex> lk(g_cache_mu);
-  hipEvent_t& ev = g_last_use[{dev, stream}];
-  if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
-  if (!ev || hipEventRecord(ev, stream) != hipSuccess) {
-    (void)hipGetLastError();
-    (void)hipStreamSynchronize(stream);  // without an event the work is waited for
-  }
-}
-
-}  // namespace
-
-CallScope::CallScope(void* s) : stream((hipStream_t)s), outer(t_scope) { t_scope = this; }
-
-CallScope::~CallScope() {
-  t_scope = outer;
-  if (released) mark_last_use(dev, stream);
-}
-
-gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what) {
-  *p = nullptr;
-  int dev = 0;
-  const bool keep = may_keep(stream, &dev);
-  if (keep) {
-    // whole 64 KiB (2 MiB above 1 MiB), so that nearly equal sizes share blocks
-    const size_t unit = bytes > (size_t(1) << 20) ? size_t(2) << 20 : size_t(64) << 10;
-    bytes = (bytes + unit - 1) / unit * unit;
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    auto best = g_idle.end();
-    for (auto it = g_idle.begin(); it != g_idle.end(); ++it)
-      if (it->dev == dev && it->stream == stream && it->bytes >= bytes &&
-          it->bytes <= bytes + bytes / 4 && (best == g_idle.end() || it->bytes < best->bytes))
-        best = it;
-    if (best != g_idle.end()) {
-      CallScope* sc = t_scope && t_scope->stream == stream ? t_scope : nullptr;
-      if (callers_stream(dev, stream) && !(sc && sc->waited)) {
-        auto ev = g_last_use.find({dev, stream});
-        if (ev != g_last_use.end() && ev->second &&
-            hipStreamWaitEvent(stream, ev->second, 0) != hipSuccess) {
-          (void)hipGetLastError();
-          (void)hipEventSynchronize(ev->second);
-        }
-        if (sc) sc->waited = true;
-      }
-      *p = best->ptr;
-      g_idle_bytes[dev] -= best->bytes;
-      g_live.emplace(best->ptr, *best);
-      g_idle.erase(best);
-      return GCN_OK;
-    }
-  }
-  hipError_t e = hipMallocAsync(p, bytes, stream);
-  if (e != hipSuccess && keep) {
-    (void)hipGetLastError();
-    for (const Block& b : take_idle(dev, 0)) give_back(b, stream);
-    (void)hipStreamSynchronize(stream);
-    e = hipMallocAsync(p, bytes, stream);
-  }
-  if (e != hipSuccess) {
-    *p = nullptr;
-    (void)hipGetLastError();
-    set_error("stream-ordered allocation of %zu bytes for %s failed: %s", bytes, what,
-              hipGetErrorString(e));
-    return GCN_ENOMEM;
-  }
-  if (keep) {
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    g_live.emplace(*p, Block{*p, bytes, dev, stream});
-  }
-  return GCN_OK;
-}
-
-void tfree(void* p, hipStream_t stream) {
-  if (!p) return;
-  int dev = 0;
-  const bool keep = may_keep(stream, &dev);
-  size_t over = 0;
-  bool kept = false, mark = false;
-  {
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    auto it = g_live.find(p);
-    if (it != g_live.end()) {
-      if (keep && it->second.dev == dev && it->second.stream == stream) {
-        if (callers_stream(dev, stream)) {
-          if (t_scope && t_scope->stream == stream) {
-            t_scope->released = true;
-            t_scope->dev = dev;
-          } else {
-            mark = true;
-          }
-        }
-        g_idle.push_back(it->second);
-        g_idle_bytes[dev] += it->second.bytes;
-        kept = true;
-        if (!g_idle_max[dev]) {
-          size_t free_b = 0, total = 0;
-          if (hipMemGetInfo(&free_b, &total) != hipSuccess) {
-            (void)hipGetLastError();
-            total = size_t(64) << 30;
-          }
-          g_idle_max[dev] = total / 4;
-        }
-        if (g_idle_bytes[dev] > g_idle_max[dev]) over = g_idle_max[dev];
-      }
-      g_live.erase(it);
-    }
-  }
-  if (!kept) {
-    (void)hipFreeAsync(p, stream);
-    return;
-  }
-  if (mark) mark_last_use(dev, stream);
-  if (over)
-    for (const Block& b : take_idle(dev, over)) give_back(b, stream);
-}
-
-void graph_opened(int dev) {
-  std::lock_guard<std::mutex> lk(g_cache_mu);
-  if (dev >= 0 && dev < 64) ++g_graphs[dev];
-}
-
-void graph_closed(int dev) {
-  {
-    std::lock_guard<std::mutex> lk(g_cache_mu);
-    if (dev < 0 || dev >= 64 || --g_graphs[dev] > 0) return;
-  }
-  int cur = -1;
-  if (hipGetDevice(&cur) != hipSuccess || cur != dev) return;
-  for (const Block& b : take_idle(dev, kKeepIdle)) (void)hipFree(b.ptr);
 }
 
 gcn_status check_graph(const gcn_graph* g) {
