@@ -36,10 +36,12 @@ void dfree(void* p) {
 // them without waiting, since its work is ordered behind the work that used them.
 //  * A caller's stream may be destroyed with its work pending and a new one
 //    created at its address. So a call that released blocks ends with an event
-//    on its stream, and the first block taken by a later call at that address
-//    waits for it: nothing to wait for on the stream itself, and a real
-//    dependency on another. The NULL stream and the library's own are not
-//    destroyed and need no event.
+//    on its stream, and a later call at that address waits for it before it takes
+//    a block and before it records the event again: nothing to wait for on the
+//    stream itself, and a real dependency on another. (A call that finds no block
+//    of its size waits too, or the event would no longer cover the work of the
+//    stream before.) The NULL stream and the library's own are not destroyed and
+//    need no event.
 //  * A block goes to another stream only through the driver.
 //  * While a stream is being captured, its temporaries are nodes of the graph
 //    (hipMallocAsync / hipFreeAsync), as a graph may be replayed on any stream.
@@ -115,9 +117,21 @@ std::list<Block> take_idle(int dev, size_t keep) {
   return out;
 }
 
-// The event that ends the last call on a caller's stream that released blocks.
-void mark_last_use(int dev, hipStream_t stream) {
+// The stream waits for the event at its address (the caller holds the lock).
+void wait_last_use(int dev, hipStream_t stream) {
+  auto ev = g_last_use.find({dev, stream});
+  if (ev == g_last_use.end() || !ev->second) return;
+  if (hipStreamWaitEvent(stream, ev->second, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipEventSynchronize(ev->second);
+  }
+}
+
+// The event that ends the last call on a caller's stream that released blocks
+// (waited: the call has waited for the one before).
+void mark_last_use(int dev, hipStream_t stream, bool waited) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
+  if (!waited) wait_last_use(dev, stream);
   hipEvent_t& ev = g_last_use[{dev, stream}];
   if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
   if (!ev || hipEventRecord(ev, stream) != hipSuccess) {
@@ -132,7 +146,7 @@ CallScope::CallScope(void* s) : stream((hipStream_t)s), outer(t_scope) { t_scope
 
 CallScope::~CallScope() {
   t_scope = outer;
-  if (released) mark_last_use(dev, stream);
+  if (released) mark_last_use(dev, stream, waited);
 }
 
 gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what) {
@@ -152,12 +166,7 @@ gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what)
     if (best != g_idle.end()) {
       CallScope* sc = t_scope && t_scope->stream == stream ? t_scope : nullptr;
       if (callers_stream(dev, stream) && !(sc && sc->waited)) {
-        auto ev = g_last_use.find({dev, stream});
-        if (ev != g_last_use.end() && ev->second &&
-            hipStreamWaitEvent(stream, ev->second, 0) != hipSuccess) {
-          (void)hipGetLastError();
-          (void)hipEventSynchronize(ev->second);
-        }
+        wait_last_use(dev, stream);
         if (sc) sc->waited = true;
       }
       *p = best->ptr;
@@ -227,7 +236,7 @@ void tfree(void* p, hipStream_t stream) {
     (void)hipFreeAsync(p, stream);
     return;
   }
-  if (mark) mark_last_use(dev, stream);
+  if (mark) mark_last_use(dev, stream, false);
   if (over)
     for (const Block& b : take_idle(dev, over)) give_back(b, stream);
 }

@@ -1,0 +1,91 @@
+// Runs the library's device memory code against the model of the HIP calls:
+// no block may be used, or given back, while earlier work on it may be running.
+// usage: model SCENARIO SEED; prints the number of faults.
+#include <cstdarg>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <random>
+#include <vector>
+
+#include "../../paper_2411_16025_amd/csrc/workspace.hip"
+
+namespace gcn {
+void set_error(const char*, ...) {}
+static model::Stream g_side_stream{-1, {}};
+hipStream_t side_stream(int) { return &g_side_stream; }
+}  // namespace gcn
+
+using namespace gcn;
+
+// Streams whose addresses are taken again after they are destroyed.
+struct Streams {
+  std::vector<model::Stream> slot = std::vector<model::Stream>(3);
+  std::vector<bool> live = std::vector<bool>(3, false);
+  hipStream_t create(int i) {
+    slot[i] = model::Stream{model::st().next_id++, {}};
+    live[i] = true;
+    return &slot[i];
+  }
+};
+
+static void call(hipStream_t s, const std::vector<size_t>& sizes, bool scoped = true,
+                 bool side = false) {
+  alignas(CallScope) char buf[sizeof(CallScope)];
+  CallScope* sc = scoped ? new (buf) CallScope(s) : nullptr;
+  std::vector<void*> p(sizes.size());
+  for (size_t i = 0; i < sizes.size(); ++i)
+    if (tmalloc(&p[i], sizes[i], s, "block") != GCN_OK) p[i] = nullptr;
+  for (void* q : p)
+    if (q) model::use(q, s);
+  if (side) {  // fork, a block of the side stream and one of the caller's, join
+    hipStream_t s2 = side_stream(0);
+    model::join(s2->clock, model::now(s));
+    void* q = nullptr;
+    if (tmalloc(&q, sizes[0], s2, "side block") == GCN_OK) model::use(q, s2);
+    tfree(q, s2);
+    if (p[0]) model::use(p[0], s2);
+    model::join(model::at(s).clock, s2->clock);
+  }
+  for (void* q : p) tfree(q, s);
+  if (sc) sc->~CallScope();
+}
+
+static size_t kib(int n) { return (size_t)n << 10; }
+
+int main(int argc, char** argv) {
+  model::State& st = model::st();
+  st.total = kib(64 << 10);
+  const char* what = argv[1];
+  std::mt19937 rng(argc > 2 ? atoi(argv[2]) : 0);
+  Streams S;
+  if (!strcmp(what, "address")) {
+    // a stream destroyed with its work pending; the first call at its address
+    // finds no block of its size, the second one does
+    call(S.create(0), {kib(64)});
+    hipStream_t s = S.create(0);
+    call(s, {kib(640)});
+    call(s, {kib(64)});
+  } else if (!strcmp(what, "address_unscoped")) {
+    call(S.create(0), {kib(64)}, false);
+    hipStream_t s = S.create(0);
+    call(s, {kib(640)}, false);
+    call(s, {kib(64)}, false);
+  } else if (!strcmp(what, "random")) {
+    for (int step = 0; step < 400; ++step) {
+      const int i = rng() % 4;
+      if (i < 3 && (!S.live[i] || rng() % 6 == 0)) S.create(i);
+      hipStream_t s = i < 3 ? &S.slot[i] : nullptr;
+      std::vector<size_t> sizes(1 + rng() % 4);
+      for (size_t& b : sizes) b = kib(64 << rng() % 7);
+      call(s, sizes, rng() % 4 != 0, rng() % 3 == 0);
+      if (rng() % 20 == 0) graph_opened(0);
+      if (rng() % 40 == 0) graph_closed(0);
+      if (rng() % 15 == 0) hipStreamSynchronize(s);
+    }
+  } else {
+    return 2;
+  }
+  printf("faults %d allocs %d frees %d\n", st.faults, st.allocs, st.frees);
+  return st.faults != 0;
+}
