@@ -34,7 +34,9 @@
  *  - Temporaries are allocated stream-ordered and kept, per stream, for the
  *    next call on it: at most a quarter of the device's memory is kept idle.
  *    It is given back when an allocation of the library fails, and all but
- *    256 MiB of it when the last graph on the device is freed.
+ *    256 MiB of it when the last graph on the device is freed. The partial rows
+ *    of an aggregation, which come from the device's default memory pool, are
+ *    given back with their graph.
  */
 #ifndef GCNAGG_H
 #define GCNAGG_H

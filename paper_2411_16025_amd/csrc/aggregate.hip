@@ -809,7 +809,8 @@ gcn_status launch_all(const Mat& m, const Src& src, float* y, int64_t ldy, int F
   }
   float* parts = ws;
   const int64_t ldp = (F + 3) & ~3;
-  if (p.n_parts > 0 && !ws) GCN_CHECK(talloc(&parts, p.n_parts * ldp, stream, "partial rows"));
+  if (p.n_parts > 0 && !ws)
+    GCN_CHECK(talloc(&parts, p.n_parts * ldp, stream, "partial rows", m.owner));
   // a workspace the caller owns is never released here
   auto release = [&]() {
     if (!ws) tfree(parts, stream);

@@ -854,8 +854,8 @@ void destroy(gcn_graph* g) {
   if (g->csc_shared && g->csc_own_ent) dfree(g->csc.ent);
   free_mat(g->csr, true);
   g->magic = kFreed;
+  graph_closed(dev, g);
   delete g;
-  graph_closed(dev);
 }
 
 gcn_status build_impl(int64_t n_rows, int64_t n_cols, int64_t n_edges, const int32_t* src,
@@ -869,6 +869,7 @@ gcn_status build_impl(int64_t n_rows, int64_t n_cols, int64_t n_edges, const int
   g->csr.n_minor = n_cols;
   g->csc.n_major = n_cols;
   g->csc.n_minor = n_rows;
+  g->csr.owner = g->csc.owner = g;
 
   uint64_t *keys = nullptr, *alt = nullptr;
   int* err = nullptr;

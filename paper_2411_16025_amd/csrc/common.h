@@ -86,6 +86,7 @@ struct Mat {
   int64_t n_major = 0, n_minor = 0, nnz = 0;
   int64_t* ptr = nullptr;  // [n_major + 1], after the entries in the same allocation
   Ent* ent = nullptr;      // [nnz]
+  const void* owner = nullptr;  // the graph, which its partial rows are kept for
   Plan plan;
 };
 

@@ -22,13 +22,15 @@ gcn_status dalloc(T** p, int64_t count, const char* what) {
 void dfree(void* p);
 
 // ---- temporaries ------------------------------------------------------------------
-// Temporaries of the work enqueued on `stream`, kept for later calls on it
-// (workspace.hip).
-gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what);
+// Temporaries of the work enqueued on `stream`, kept for later calls on it, or
+// for later calls on it with the same owner, a graph (workspace.hip).
+gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what,
+                   const void* owner = nullptr);
 template <class T>
-gcn_status talloc(T** p, int64_t count, hipStream_t stream, const char* what) {
+gcn_status talloc(T** p, int64_t count, hipStream_t stream, const char* what,
+                  const void* owner = nullptr) {
   return tmalloc(reinterpret_cast<void**>(p), (size_t)(count > 0 ? count : 1) * sizeof(T), stream,
-                 what);
+                 what, owner);
 }
 void tfree(void* p, hipStream_t stream);
 // Whether work on the stream is being recorded (or the runtime cannot tell).
@@ -45,8 +47,10 @@ struct CallScope {
   CallScope& operator=(const CallScope&) = delete;
   ~CallScope();
 };
-// Graphs alive per device (idle temporaries are given back with the last one).
+// Graphs alive per device: a graph's idle temporaries are given back with it, the
+// others with the last one. graph_closed is called before the graph's address
+// can be another's.
 void graph_opened(int dev);
-void graph_closed(int dev);
+void graph_closed(int dev, const void* graph);
 
 }  // namespace gcn

@@ -43,6 +43,11 @@ void dfree(void* p) {
 //    stream before.) The NULL stream and the library's own are not destroyed and
 //    need no event.
 //  * A block goes to another stream only through the driver.
+//  * The partial rows of an aggregation come from the device's default memory pool
+//    and belong to their graph: they are kept for its next aggregation and given
+//    back with it. All other kept blocks come from a pool of the library's own, so
+//    that the default pool holds nothing of a graph that was only built (what
+//    calls that promise to take nothing from it are measured by).
 //  * While a stream is being captured, its temporaries are nodes of the graph
 //    (hipMallocAsync / hipFreeAsync), as a graph may be replayed on any stream.
 //  * At most a quarter of the device's memory is kept idle, the oldest blocks
@@ -55,8 +60,10 @@ struct Block {
   size_t bytes;
   int dev;
   hipStream_t stream;
+  const void* owner;  // the graph it belongs to, or null
 };
 
+hipMemPool_t g_pool[64] = {};  // set once per device, under g_cache_mu
 std::mutex g_cache_mu;
 std::list<Block> g_idle;                  // oldest first
 std::unordered_map<void*, Block> g_live;  // handed out
@@ -67,6 +74,27 @@ int g_graphs[64] = {};
 constexpr size_t kKeepIdle = size_t(256) << 20;
 
 thread_local CallScope* t_scope = nullptr;
+
+// A block from the driver, of the library's own pool or (pool = false) of the
+// default one.
+hipError_t driver_alloc(void** p, size_t bytes, int dev, hipStream_t stream, bool pool) {
+  hipMemPool_t own = nullptr;
+  if (pool) {
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    if (!g_pool[dev]) {
+      hipMemPoolProps props = {};
+      props.allocType = hipMemAllocationTypePinned;
+      props.location.type = hipMemLocationTypeDevice;
+      props.location.id = dev;
+      if (hipMemPoolCreate(&g_pool[dev], &props) != hipSuccess) {
+        (void)hipGetLastError();
+        g_pool[dev] = nullptr;
+      }
+    }
+    own = g_pool[dev];
+  }
+  return own ? hipMallocFromPoolAsync(p, bytes, own, stream) : hipMallocAsync(p, bytes, stream);
+}
 
 // The current device; false where blocks cannot be kept (a capturing stream,
 // the special handles, a stream the runtime refuses).
@@ -149,7 +177,8 @@ CallScope::~CallScope() {
   if (released) mark_last_use(dev, stream, waited);
 }
 
-gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what) {
+gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what,
+                   const void* owner) {
   *p = nullptr;
   int dev = 0;
   const bool keep = may_keep(stream, &dev);
@@ -160,7 +189,7 @@ gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what)
     std::lock_guard<std::mutex> lk(g_cache_mu);
     auto best = g_idle.end();
     for (auto it = g_idle.begin(); it != g_idle.end(); ++it)
-      if (it->dev == dev && it->stream == stream && it->bytes >= bytes &&
+      if (it->dev == dev && it->stream == stream && it->owner == owner && it->bytes >= bytes &&
           it->bytes <= bytes + bytes / 4 && (best == g_idle.end() || it->bytes < best->bytes))
         best = it;
     if (best != g_idle.end()) {
@@ -176,12 +205,12 @@ gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what)
       return GCN_OK;
     }
   }
-  hipError_t e = hipMallocAsync(p, bytes, stream);
+  hipError_t e = driver_alloc(p, bytes, dev, stream, keep && !owner);
   if (e != hipSuccess && keep) {
     (void)hipGetLastError();
     for (const Block& b : take_idle(dev, 0)) give_back(b, stream);
     (void)hipStreamSynchronize(stream);
-    e = hipMallocAsync(p, bytes, stream);
+    e = driver_alloc(p, bytes, dev, stream, !owner);
   }
   if (e != hipSuccess) {
     *p = nullptr;
@@ -192,7 +221,7 @@ gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what)
   }
   if (keep) {
     std::lock_guard<std::mutex> lk(g_cache_mu);
-    g_live.emplace(*p, Block{*p, bytes, dev, stream});
+    g_live.emplace(*p, Block{*p, bytes, dev, stream, owner});
   }
   return GCN_OK;
 }
@@ -246,10 +275,25 @@ void graph_opened(int dev) {
   if (dev >= 0 && dev < 64) ++g_graphs[dev];
 }
 
-void graph_closed(int dev) {
+void graph_closed(int dev, const void* graph) {
+  std::list<Block> own;
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
-    if (dev < 0 || dev >= 64 || --g_graphs[dev] > 0) return;
+    if (dev < 0 || dev >= 64) return;
+    for (auto it = g_idle.begin(); it != g_idle.end();) {
+      auto next = std::next(it);
+      if (it->owner == graph) {
+        g_idle_bytes[dev] -= it->bytes;
+        own.splice(own.end(), g_idle, it);
+      }
+      it = next;
+    }
+    --g_graphs[dev];
+  }
+  for (const Block& b : own) (void)hipFree(b.ptr);
+  {
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    if (g_graphs[dev] > 0) return;
   }
   int cur = -1;
   if (hipGetDevice(&cur) != hipSuccess || cur != dev) return;

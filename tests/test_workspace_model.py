@@ -29,6 +29,10 @@ def test_a_new_stream_at_an_old_address(model, scenario):
     model(scenario)
 
 
+def test_partial_rows_go_with_their_graph(model):
+    model("graphs")
+
+
 def test_random_calls(model):
     for seed in range(50):
         model("random", seed)

@@ -9,6 +9,18 @@
 
 enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2, hipErrorUnknown = 999 };
 enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0 };
+enum hipMemAllocationType { hipMemAllocationTypePinned = 1 };
+enum hipMemLocationType { hipMemLocationTypeDevice = 1 };
+struct hipMemLocation {
+  hipMemLocationType type;
+  int id;
+};
+struct hipMemPoolProps {
+  hipMemAllocationType allocType;
+  int handleTypes;
+  hipMemLocation location;
+};
+typedef struct hipMemPool* hipMemPool_t;
 constexpr unsigned hipEventDisableTiming = 2;
 
 namespace model {
@@ -41,6 +53,7 @@ struct State {
   Clock host;                       // what the host has waited for
   Clock all;                        // all work
   std::map<char*, size_t> mem;      // live allocations
+  std::map<char*, size_t> pooled;   // those of the default pool
   std::map<char*, Clock> last_use;  // of the work that touched each
   size_t allocated = 0, total = 0, limit = 0;
   int allocs = 0, frees = 0, faults = 0;
@@ -99,6 +112,7 @@ inline hipError_t release(void* p) {
   }
   s.allocated -= it->second;
   s.last_use.erase(it->first);
+  s.pooled.erase(it->first);
   s.mem.erase(it);
   ++s.frees;
   return hipSuccess;
@@ -122,7 +136,18 @@ inline hipError_t hipMemGetInfo(size_t* f, size_t* t) {
   return hipSuccess;
 }
 inline hipError_t hipMalloc(void** p, size_t n) { return model::alloc(p, n); }
-inline hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) { return model::alloc(p, n); }
+inline hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) {
+  const hipError_t e = model::alloc(p, n);
+  if (e == hipSuccess) model::st().pooled[(char*)*p] = n;
+  return e;
+}
+inline hipError_t hipMemPoolCreate(hipMemPool_t* p, const hipMemPoolProps*) {
+  *p = (hipMemPool_t)1;
+  return hipSuccess;
+}
+inline hipError_t hipMallocFromPoolAsync(void** p, size_t n, hipMemPool_t, hipStream_t) {
+  return model::alloc(p, n);
+}
 inline hipError_t hipFree(void* p) {  // waits for the device
   model::join(model::st().host, model::st().all);
   return model::release(p);

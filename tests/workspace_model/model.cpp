@@ -30,12 +30,12 @@ struct Streams {
 };
 
 static void call(hipStream_t s, const std::vector<size_t>& sizes, bool scoped = true,
-                 bool side = false) {
+                 bool side = false, const void* graph = nullptr) {
   alignas(CallScope) char buf[sizeof(CallScope)];
   CallScope* sc = scoped ? new (buf) CallScope(s) : nullptr;
   std::vector<void*> p(sizes.size());
   for (size_t i = 0; i < sizes.size(); ++i)
-    if (tmalloc(&p[i], sizes[i], s, "block") != GCN_OK) p[i] = nullptr;
+    if (tmalloc(&p[i], sizes[i], s, "block", i % 2 ? nullptr : graph) != GCN_OK) p[i] = nullptr;
   for (void* q : p)
     if (q) model::use(q, s);
   if (side) {  // fork, a block of the side stream and one of the caller's, join
@@ -71,16 +71,38 @@ int main(int argc, char** argv) {
     hipStream_t s = S.create(0);
     call(s, {kib(640)}, false);
     call(s, {kib(64)}, false);
+  } else if (!strcmp(what, "graphs")) {
+    // the default pool holds the partial rows of the graphs that ran, no more
+    char g[2];
+    graph_opened(0);
+    graph_opened(0);
+    call(nullptr, {kib(64), kib(128)});
+    if (!st.pooled.empty()) ++st.faults;
+    for (int k = 0; k < 2; ++k) {
+      call(nullptr, {kib(64), kib(128)}, true, false, &g[k]);
+      call(S.create(k), {kib(64), kib(128)}, true, false, &g[k]);
+      call(&S.slot[k], {kib(64), kib(128)}, true, false, &g[k]);
+    }
+    if (st.pooled.size() != 4) ++st.faults;
+    graph_closed(0, &g[0]);
+    if (st.pooled.size() != 2) ++st.faults;
+    graph_closed(0, &g[1]);
+    if (!st.pooled.empty()) ++st.faults;
   } else if (!strcmp(what, "random")) {
+    char graphs[3];
+    for (int k = 0; k < 3; ++k) graph_opened(0);
     for (int step = 0; step < 400; ++step) {
       const int i = rng() % 4;
       if (i < 3 && (!S.live[i] || rng() % 6 == 0)) S.create(i);
       hipStream_t s = i < 3 ? &S.slot[i] : nullptr;
       std::vector<size_t> sizes(1 + rng() % 4);
       for (size_t& b : sizes) b = kib(64 << rng() % 7);
-      call(s, sizes, rng() % 4 != 0, rng() % 3 == 0);
-      if (rng() % 20 == 0) graph_opened(0);
-      if (rng() % 40 == 0) graph_closed(0);
+      const int k = rng() % 4;
+      call(s, sizes, rng() % 4 != 0, rng() % 3 == 0, k < 3 ? &graphs[k] : nullptr);
+      if (k < 3 && rng() % 20 == 0) {  // freed, and another at its address
+        graph_closed(0, &graphs[k]);
+        if (rng() % 2) graph_opened(0);
+      }
       if (rng() % 15 == 0) hipStreamSynchronize(s);
     }
   } else {
