@@ -388,7 +388,8 @@ void sage_free(Sage& m, hipStream_t s) {
 // Shapes, buffers, packed weights and the forward pass; on return L[2].o
 // holds the logits and L[0..1].o the ReLU outputs of layers 1 and 2. The
 // caller's H1 and H2 take the place of L[0..1].o where they have their layout
-// (2.45M x 256: a copy of each took 0.9 ms).
+// (2.45M x 256: a copy of each took 0.9 ms) and no padding columns: those the
+// products write too, and in the caller's rows they are the caller's.
 gcn_status sage_forward(const gcn_graph* g, const float* X, int64_t ldx, int64_t f_in,
                         int64_t hidden, int64_t n_classes, const float* const* params,
                         const int32_t* labels, const uint8_t* lp_mask, const float* E, double eps,
@@ -405,7 +406,8 @@ gcn_status sage_forward(const gcn_graph* g, const float* X, int64_t ldx, int64_t
     if (st == GCN_OK) st = talloc(&L[l].rstd, n, s, "LayerNorm 1/std");
     if (st == GCN_OK) st = talloc(&L[l].wp, L[l].K * L[l].fop, s, "packed weights");
     float* out = l == 0 ? H1 : (l == 1 ? H2 : nullptr);
-    if (out && (l == 0 ? ldh1 : ldh2) == L[l].fop && reinterpret_cast<uintptr_t>(out) % 16 == 0) {
+    if (out && L[l].fo == L[l].fop && (l == 0 ? ldh1 : ldh2) == L[l].fop &&
+        reinterpret_cast<uintptr_t>(out) % 16 == 0) {
       L[l].o = out;
       L[l].own_o = false;
     } else if (st == GCN_OK) {

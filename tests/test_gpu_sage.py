@@ -296,3 +296,35 @@ def test_sage_step_edge_cases(G, n, f_in, hidden, C, mask_kind):
         return
     check_against_oracle(og, X, params, y, mask, E, masks, [H1, H2], host(logits), got_loss, got,
                          host(dE))
+
+
+@pytest.mark.parametrize("hidden,ld1,ld2", [(30, 32, 32), (47, 48, 48), (32, 32, 32), (31, 31, 40)])
+def test_forward_writes_only_its_columns(G, hidden, ld1, ld2):
+    """H1 and H2 as views of wider rows, the last one ending with its columns:
+    what lies between and behind them stays, and the columns are those of
+    contiguous outputs."""
+    import ctypes
+    import torch
+    note("sage3 forward into rows of %d and %d of hidden=%d" % (ld1, ld2, hidden))
+    n, f_in, C = 501, 20, 7
+    src, dst, X, params, y, mask, E = sage_case(n, 4000, f_in, hidden, C, 480, False)
+    g = G.gcn_build_csr(n, n, dev(src), dev(dst), synth.SYMMETRIZE)
+    G.gcn_normalize_mean(g)
+    Xd, pd = dev(X), [dev(p) for p in params]
+    h1, h2, logits = G.gcn_sage3_forward(g, Xd, pd)
+    out = [torch.full((n * ld + 64,), 7.0, device="cuda:0") for ld in (ld1, ld2)]
+    z = torch.empty((n, C), device="cuda:0")
+    ptrs = (ctypes.c_void_p * 9)(*[p.data_ptr() for p in pd])
+    rc = G.lib().gcn_sage3_forward(g.handle, Xd.data_ptr(), f_in, f_in, hidden, C, ptrs, None, None,
+                                   None, 1e-5, out[0].data_ptr(), ld1, out[1].data_ptr(), ld2,
+                                   z.data_ptr(), C, None)
+    assert rc == 0
+    torch.cuda.synchronize()
+    for o, ld, want in ((out[0], ld1, h1), (out[1], ld2, h2)):
+        got = host(o)
+        used = np.zeros(got.size, bool)
+        used[:n * ld].reshape(n, ld)[:, :hidden] = True
+        assert np.array_equal(got[used].view(np.uint32), host(want).ravel().view(np.uint32))
+        assert np.all(got[~used] == 7.0)
+    assert torch.equal(z, logits)
+    g.free()
