@@ -11,19 +11,6 @@
 
 namespace gcn {
 
-gcn_status dmalloc(void** p, size_t bytes, const char* what) {
-  *p = nullptr;
-  hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess) {
-    *p = nullptr;
-    (void)hipGetLastError();
-    set_error("device allocation of %zu bytes for %s failed: %s", bytes, what,
-              hipGetErrorString(e));
-    return GCN_ENOMEM;
-  }
-  return GCN_OK;
-}
-
 void dfree(void* p) {
   if (p) (void)hipFree(p);
 }
@@ -169,6 +156,25 @@ void mark_last_use(int dev, hipStream_t stream, bool waited) {
 }
 
 }  // namespace
+
+gcn_status dmalloc(void** p, size_t bytes, const char* what) {
+  *p = nullptr;
+  hipError_t e = hipMalloc(p, bytes);
+  int dev = 0;
+  if (e != hipSuccess && hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
+    (void)hipGetLastError();
+    for (const Block& b : take_idle(dev, 0)) (void)hipFree(b.ptr);
+    e = hipMalloc(p, bytes);
+  }
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+    set_error("device allocation of %zu bytes for %s failed: %s", bytes, what,
+              hipGetErrorString(e));
+    return GCN_ENOMEM;
+  }
+  return GCN_OK;
+}
 
 CallScope::CallScope(void* s) : stream((hipStream_t)s), outer(t_scope) { t_scope = this; }
 

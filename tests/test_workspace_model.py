@@ -33,6 +33,10 @@ def test_partial_rows_go_with_their_graph(model):
     model("graphs")
 
 
+def test_idle_memory_is_given_back_for_an_allocation(model):
+    model("memory")
+
+
 def test_random_calls(model):
     for seed in range(50):
         model("random", seed)

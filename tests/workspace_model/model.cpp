@@ -88,6 +88,17 @@ int main(int argc, char** argv) {
     if (st.pooled.size() != 2) ++st.faults;
     graph_closed(0, &g[1]);
     if (!st.pooled.empty()) ++st.faults;
+  } else if (!strcmp(what, "memory")) {
+    // 40 MiB of memory, 12 of them idle: both kinds of allocation find room
+    st.limit = kib(40 << 10);
+    void *a = nullptr, *b = nullptr;
+    call(nullptr, {kib(4 << 10), kib(8 << 10)});
+    if (dmalloc(&a, kib(32 << 10), "array") != GCN_OK) ++st.faults;
+    if (dmalloc(&b, kib(16 << 10), "array") != GCN_ENOMEM || b) ++st.faults;
+    dfree(a);
+    call(S.create(0), {kib(4 << 10), kib(8 << 10)});
+    call(nullptr, {kib(32 << 10)});
+    if (st.allocated > st.limit || st.allocs != 6) ++st.faults;
   } else if (!strcmp(what, "random")) {
     char graphs[3];
     for (int k = 0; k < 3; ++k) graph_opened(0);
