@@ -1,5 +1,8 @@
 // Device memory: the graphs' arrays and the calls' temporaries.
 
+#include <algorithm>
+#include <atomic>
+#include <cstdlib>
 #include <iterator>
 #include <list>
 #include <map>
@@ -37,9 +40,10 @@ void dfree(void* p) {
 //    calls that promise to take nothing from it are measured by).
 //  * While a stream is being captured, its temporaries are nodes of the graph
 //    (hipMallocAsync / hipFreeAsync), as a graph may be replayed on any stream.
-//  * At most a quarter of the device's memory is kept idle, the oldest blocks
-//    going first; all of it is given back when an allocation fails, and all
-//    but kKeepIdle when the last graph on the device is freed.
+//  * At most a quarter of the device's memory is kept idle (or GCN_IDLE_MAX bytes,
+//    if that is less when a graph is built), the oldest blocks going first; all of
+//    it is given back when an allocation fails, and all but kKeepIdle when the
+//    last graph on the device is freed.
 namespace {
 
 struct Block {
@@ -61,6 +65,22 @@ int g_graphs[64] = {};
 constexpr size_t kKeepIdle = size_t(256) << 20;
 
 thread_local CallScope* t_scope = nullptr;
+
+// The bytes that may be kept idle on the current device, dev.
+size_t idle_max(int dev) {
+  static std::atomic<size_t> memory[64] = {};
+  size_t free_b = 0, total = memory[dev];
+  if (!total) {
+    if (hipMemGetInfo(&free_b, &total) != hipSuccess) {
+      (void)hipGetLastError();
+      total = size_t(64) << 30;
+    }
+    memory[dev] = total;
+  }
+  const char* s = std::getenv("GCN_IDLE_MAX");
+  const long long v = s && *s ? std::atoll(s) : 0;
+  return v > 0 && (size_t)v < total / 4 ? (size_t)v : total / 4;
+}
 
 // A block from the driver, of the library's own pool or (pool = false) of the
 // default one.
@@ -254,14 +274,7 @@ void tfree(void* p, hipStream_t stream) {
         g_idle.push_back(it->second);
         g_idle_bytes[dev] += it->second.bytes;
         kept = true;
-        if (!g_idle_max[dev]) {
-          size_t free_b = 0, total = 0;
-          if (hipMemGetInfo(&free_b, &total) != hipSuccess) {
-            (void)hipGetLastError();
-            total = size_t(64) << 30;
-          }
-          g_idle_max[dev] = total / 4;
-        }
+        if (!g_idle_max[dev]) g_idle_max[dev] = idle_max(dev);
         if (g_idle_bytes[dev] > g_idle_max[dev]) over = g_idle_max[dev];
       }
       g_live.erase(it);
@@ -277,8 +290,11 @@ void tfree(void* p, hipStream_t stream) {
 }
 
 void graph_opened(int dev) {
+  if (dev < 0 || dev >= 64) return;
+  const size_t max = idle_max(dev);
   std::lock_guard<std::mutex> lk(g_cache_mu);
-  if (dev >= 0 && dev < 64) ++g_graphs[dev];
+  ++g_graphs[dev];
+  g_idle_max[dev] = max;
 }
 
 void graph_closed(int dev, const void* graph) {
@@ -303,7 +319,7 @@ void graph_closed(int dev, const void* graph) {
   }
   int cur = -1;
   if (hipGetDevice(&cur) != hipSuccess || cur != dev) return;
-  for (const Block& b : take_idle(dev, kKeepIdle)) (void)hipFree(b.ptr);
+  for (const Block& b : take_idle(dev, std::min(kKeepIdle, idle_max(dev)))) (void)hipFree(b.ptr);
 }
 
 }  // namespace gcn

@@ -2,6 +2,7 @@
 streams that come and go, give the bits of the same calls one after another."""
 
 import ctypes
+import os
 import threading
 
 import numpy as np
@@ -93,3 +94,29 @@ def test_more_than_is_kept(case):
         g.free()
     torch.cuda.synchronize()
     assert _same(torch, work(0), ref[0])
+
+
+def test_blocks_past_the_limit_go_while_their_work_is_pending(case):
+    torch, G, work, ref = case
+    note("workspace: a limit of 1 MiB")
+    tiny = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+    old = os.environ.get("GCN_IDLE_MAX")
+    os.environ["GCN_IDLE_MAX"] = str(1 << 20)
+    try:
+        G.gcn_build_csr(1, 1, tiny, tiny, 0).free()  # the limit is read with a graph
+        streams = [torch.cuda.Stream() for _ in range(2)]
+        torch.cuda.synchronize()
+        out = []
+        for rep in range(6):  # no waiting between the calls
+            for k, s in enumerate(streams):
+                with torch.cuda.stream(s):
+                    out.append((k, work(k)))
+            out.append((2, work(2)))
+        torch.cuda.synchronize()
+        assert all(_same(torch, y, ref[k]) for k, y in out)
+    finally:
+        if old is None:
+            del os.environ["GCN_IDLE_MAX"]
+        else:
+            os.environ["GCN_IDLE_MAX"] = old
+        G.gcn_build_csr(1, 1, tiny, tiny, 0).free()

@@ -37,6 +37,10 @@ def test_idle_memory_is_given_back_for_an_allocation(model):
     model("memory")
 
 
+def test_idle_memory_has_a_limit(model):
+    model("limits")
+
+
 def test_random_calls(model):
     for seed in range(50):
         model("random", seed)

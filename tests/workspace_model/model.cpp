@@ -55,7 +55,7 @@ static size_t kib(int n) { return (size_t)n << 10; }
 
 int main(int argc, char** argv) {
   model::State& st = model::st();
-  st.total = kib(64 << 10);
+  st.total = kib(64 << 10);  // at most 16 MiB idle
   const char* what = argv[1];
   std::mt19937 rng(argc > 2 ? atoi(argv[2]) : 0);
   Streams S;
@@ -99,8 +99,27 @@ int main(int argc, char** argv) {
     call(S.create(0), {kib(4 << 10), kib(8 << 10)});
     call(nullptr, {kib(32 << 10)});
     if (st.allocated > st.limit || st.allocs != 6) ++st.faults;
+  } else if (!strcmp(what, "limits")) {
+    // idle memory stays within the limit and the oldest blocks go first, whatever
+    // stream their work is on
+    graph_opened(0);
+    for (int i = 0; i < 12; ++i) call(i % 2 ? nullptr : S.create(i / 2 % 3), {kib((2 + i) << 10)});
+    if (st.allocated > st.total / 4 || st.allocated < kib(12 << 10)) ++st.faults;
+    setenv("GCN_IDLE_MAX", "4194304", 1);
+    graph_opened(0);
+    call(nullptr, {kib(1 << 10), kib(4 << 10), kib(2 << 10)});
+    if (st.allocated > kib(4 << 10)) ++st.faults;
+    setenv("GCN_IDLE_MAX", "1048576", 1);
+    char g[2];
+    graph_closed(0, &g[0]);
+    if (st.allocated <= kib(1 << 10)) ++st.faults;
+    graph_closed(0, &g[1]);
+    if (st.allocated > kib(1 << 10)) ++st.faults;
   } else if (!strcmp(what, "random")) {
     char graphs[3];
+    char limit[32];
+    snprintf(limit, sizeof(limit), "%zu", kib(64 << rng() % 8));
+    setenv("GCN_IDLE_MAX", limit, 1);
     for (int k = 0; k < 3; ++k) graph_opened(0);
     for (int step = 0; step < 400; ++step) {
       const int i = rng() % 4;
