@@ -7,6 +7,7 @@
 #include <list>
 #include <map>
 #include <mutex>
+#include <new>
 #include <unordered_map>
 #include <utility>
 
@@ -137,6 +138,24 @@ void give_back(const Block& b, hipStream_t stream) {
     (void)hipFree(b.ptr);
 }
 
+// The lists never throw (the caller holds the lock): a block that cannot be
+// noted as handed out, or as idle, goes back to the driver when it is released.
+void track(const Block& b) {
+  try {
+    g_live.emplace(b.ptr, b);
+  } catch (const std::bad_alloc&) {
+  }
+}
+
+bool push_idle(const Block& b) {
+  try {
+    g_idle.push_back(b);
+    return true;
+  } catch (const std::bad_alloc&) {
+    return false;
+  }
+}
+
 // Idle blocks of a device, oldest first, until at most keep bytes are left.
 std::list<Block> take_idle(int dev, size_t keep) {
   std::list<Block> out;
@@ -167,8 +186,13 @@ void wait_last_use(int dev, hipStream_t stream) {
 void mark_last_use(int dev, hipStream_t stream, bool waited) {
   std::lock_guard<std::mutex> lk(g_cache_mu);
   if (!waited) wait_last_use(dev, stream);
-  hipEvent_t& ev = g_last_use[{dev, stream}];
-  if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
+  hipEvent_t ev = nullptr;
+  try {
+    hipEvent_t& e = g_last_use[{dev, stream}];
+    if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) e = nullptr;
+    ev = e;
+  } catch (const std::bad_alloc&) {
+  }
   if (!ev || hipEventRecord(ev, stream) != hipSuccess) {
     (void)hipGetLastError();
     (void)hipStreamSynchronize(stream);  // without an event the work is waited for
@@ -226,7 +250,7 @@ gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what,
       }
       *p = best->ptr;
       g_idle_bytes[dev] -= best->bytes;
-      g_live.emplace(best->ptr, *best);
+      track(*best);
       g_idle.erase(best);
       return GCN_OK;
     }
@@ -247,7 +271,7 @@ gcn_status tmalloc(void** p, size_t bytes, hipStream_t stream, const char* what,
   }
   if (keep) {
     std::lock_guard<std::mutex> lk(g_cache_mu);
-    g_live.emplace(*p, Block{*p, bytes, dev, stream, owner});
+    track(Block{*p, bytes, dev, stream, owner});
   }
   return GCN_OK;
 }
@@ -262,7 +286,8 @@ void tfree(void* p, hipStream_t stream) {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     auto it = g_live.find(p);
     if (it != g_live.end()) {
-      if (keep && it->second.dev == dev && it->second.stream == stream) {
+      if (keep && it->second.dev == dev && it->second.stream == stream) kept = push_idle(it->second);
+      if (kept) {
         if (callers_stream(dev, stream)) {
           if (t_scope && t_scope->stream == stream) {
             t_scope->released = true;
@@ -271,9 +296,7 @@ void tfree(void* p, hipStream_t stream) {
             mark = true;
           }
         }
-        g_idle.push_back(it->second);
         g_idle_bytes[dev] += it->second.bytes;
-        kept = true;
         if (!g_idle_max[dev]) g_idle_max[dev] = idle_max(dev);
         if (g_idle_bytes[dev] > g_idle_max[dev]) over = g_idle_max[dev];
       }

@@ -44,3 +44,9 @@ def test_idle_memory_has_a_limit(model):
 def test_random_calls(model):
     for seed in range(50):
         model("random", seed)
+
+
+def test_host_memory_that_runs_out(model):
+    """No exception leaves the library, and no order is lost."""
+    for seed in range(30):
+        model("host_memory", seed)

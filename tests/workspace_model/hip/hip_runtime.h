@@ -63,6 +63,15 @@ inline State& st() {
   static State s;
   return s;
 }
+// The model's own bookkeeping, which does not fail when host memory runs out.
+inline int& own_depth() {
+  static int d = 0;
+  return d;
+}
+struct Own {
+  Own() { ++own_depth(); }
+  ~Own() { --own_depth(); }
+};
 
 }  // namespace model
 
@@ -81,6 +90,7 @@ inline Clock now(hipStream_t s) {
 }
 // A kernel on the stream that reads and writes the block.
 inline void use(void* p, hipStream_t s) {
+  Own own;
   Stream& t = at(s);
   join(t.clock, st().host);
   Clock& last = st().last_use[(char*)p];
@@ -90,6 +100,7 @@ inline void use(void* p, hipStream_t s) {
   join(st().all, t.clock);
 }
 inline hipError_t alloc(void** p, size_t n) {
+  Own own;
   State& s = st();
   if (s.limit && s.allocated + n > s.limit) {
     *p = nullptr;
@@ -104,6 +115,7 @@ inline hipError_t alloc(void** p, size_t n) {
   return hipSuccess;
 }
 inline hipError_t release(void* p) {
+  Own own;
   State& s = st();
   auto it = s.mem.find((char*)p);
   if (it == s.mem.end()) {
@@ -137,6 +149,7 @@ inline hipError_t hipMemGetInfo(size_t* f, size_t* t) {
 }
 inline hipError_t hipMalloc(void** p, size_t n) { return model::alloc(p, n); }
 inline hipError_t hipMallocAsync(void** p, size_t n, hipStream_t) {
+  model::Own own;
   const hipError_t e = model::alloc(p, n);
   if (e == hipSuccess) model::st().pooled[(char*)*p] = n;
   return e;
@@ -149,34 +162,42 @@ inline hipError_t hipMallocFromPoolAsync(void** p, size_t n, hipMemPool_t, hipSt
   return model::alloc(p, n);
 }
 inline hipError_t hipFree(void* p) {  // waits for the device
+  model::Own own;
   model::join(model::st().host, model::st().all);
   return model::release(p);
 }
 inline hipError_t hipFreeAsync(void* p, hipStream_t s) {
+  model::Own own;
   if (!model::before(model::st().last_use[(char*)p], model::now(s))) ++model::st().faults;
   return model::release(p);
 }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+  model::Own own;
   *e = new model::Event();
   return hipSuccess;
 }
 inline hipError_t hipEventDestroy(hipEvent_t e) {
+  model::Own own;
   delete e;
   return hipSuccess;
 }
 inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  model::Own own;
   e->clock = model::now(s);
   return hipSuccess;
 }
 inline hipError_t hipEventSynchronize(hipEvent_t e) {
+  model::Own own;
   model::join(model::st().host, e->clock);
   return hipSuccess;
 }
 inline hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+  model::Own own;
   model::join(model::at(s).clock, e->clock);
   return hipSuccess;
 }
 inline hipError_t hipStreamSynchronize(hipStream_t s) {
+  model::Own own;
   model::join(model::st().host, model::at(s).clock);
   return hipSuccess;
 }

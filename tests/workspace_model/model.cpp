@@ -10,6 +10,18 @@
 
 #include "../../paper_2411_16025_amd/csrc/workspace.hip"
 
+// Host memory that runs out: inside the library, every n-th allocation fails.
+static int g_fail_every = 0, g_news = 0, g_failed = 0;
+void* operator new(size_t n) {
+  if (g_fail_every && !model::own_depth() && ++g_news % g_fail_every == 0) {
+    ++g_failed;
+    throw std::bad_alloc();
+  }
+  return malloc(n ? n : 1);
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+
 namespace gcn {
 void set_error(const char*, ...) {}
 static model::Stream g_side_stream{-1, {}};
@@ -31,24 +43,32 @@ struct Streams {
 
 static void call(hipStream_t s, const std::vector<size_t>& sizes, bool scoped = true,
                  bool side = false, const void* graph = nullptr) {
+  model::Own own;  // but for the calls of the library itself
+  auto lib = [](auto f) {
+    const int depth = model::own_depth();
+    model::own_depth() = 0;
+    f();
+    model::own_depth() = depth;
+  };
   alignas(CallScope) char buf[sizeof(CallScope)];
   CallScope* sc = scoped ? new (buf) CallScope(s) : nullptr;
   std::vector<void*> p(sizes.size());
   for (size_t i = 0; i < sizes.size(); ++i)
-    if (tmalloc(&p[i], sizes[i], s, "block", i % 2 ? nullptr : graph) != GCN_OK) p[i] = nullptr;
+    lib([&] { tmalloc(&p[i], sizes[i], s, "block", i % 2 ? nullptr : graph); });
   for (void* q : p)
     if (q) model::use(q, s);
   if (side) {  // fork, a block of the side stream and one of the caller's, join
     hipStream_t s2 = side_stream(0);
     model::join(s2->clock, model::now(s));
     void* q = nullptr;
-    if (tmalloc(&q, sizes[0], s2, "side block") == GCN_OK) model::use(q, s2);
-    tfree(q, s2);
+    lib([&] { tmalloc(&q, sizes[0], s2, "side block"); });
+    if (q) model::use(q, s2);
+    lib([&] { tfree(q, s2); });
     if (p[0]) model::use(p[0], s2);
     model::join(model::at(s).clock, s2->clock);
   }
-  for (void* q : p) tfree(q, s);
-  if (sc) sc->~CallScope();
+  for (void* q : p) lib([&] { tfree(q, s); });
+  if (sc) lib([&] { sc->~CallScope(); });
 }
 
 static size_t kib(int n) { return (size_t)n << 10; }
@@ -115,13 +135,15 @@ int main(int argc, char** argv) {
     if (st.allocated <= kib(1 << 10)) ++st.faults;
     graph_closed(0, &g[1]);
     if (st.allocated > kib(1 << 10)) ++st.faults;
-  } else if (!strcmp(what, "random")) {
+  } else if (!strcmp(what, "random") || !strcmp(what, "host_memory")) {
+    if (!strcmp(what, "host_memory")) g_fail_every = 2 + rng() % 5;
     char graphs[3];
     char limit[32];
     snprintf(limit, sizeof(limit), "%zu", kib(64 << rng() % 8));
     setenv("GCN_IDLE_MAX", limit, 1);
     for (int k = 0; k < 3; ++k) graph_opened(0);
     for (int step = 0; step < 400; ++step) {
+      model::Own own;
       const int i = rng() % 4;
       if (i < 3 && (!S.live[i] || rng() % 6 == 0)) S.create(i);
       hipStream_t s = i < 3 ? &S.slot[i] : nullptr;
@@ -138,6 +160,8 @@ int main(int argc, char** argv) {
   } else {
     return 2;
   }
+  if (g_fail_every && !g_failed) ++st.faults;
+  g_fail_every = 0;
   printf("faults %d allocs %d frees %d\n", st.faults, st.allocs, st.frees);
   return st.faults != 0;
 }
