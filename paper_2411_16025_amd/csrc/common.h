@@ -222,7 +222,8 @@ gcn_status gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int
                     const float* mask = nullptr, int64_t ldm = 0, bool relu = false);
 // The same products on the bf16 matrix cores with three-part operands
 // (gemm_split.hip), any alignment, for sizes and strides that *_takes accepts.
-bool gemm_split_tall_takes(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldc, int64_t ldm);
+bool gemm_split_tall_takes(int op, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                           int64_t ldc, int64_t ldm);
 bool gemm_split_tn_takes(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb);
 gcn_status gemm_split_tall(int op, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                            const float* B, int64_t ldb, float* C, int64_t ldc, const float* mask,

@@ -1739,22 +1739,18 @@ gcn_status gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int
     return GCN_OK;
   }
   // Three-part products on the bf16 matrix cores: outputs of more than 128
-  // columns, and of more than 64 once the product outweighs packing B (us, the
-  // tiles here -> three parts: 1,000 x 256 x 100 16.5 -> 13.4, x 516 63 -> 32;
-  // 30,000 x 128 x 256 28 -> 22; 3,000 x 128 x 256 19.6 -> 19.5, x 100 x 64 8.4 ->
-  // 12.2), and every unaligned one that is not tiny (the general kernel loads
-  // element by element: 500,000 x 47 x 256 418 us, 170). Narrower aligned
-  // outputs are bound by reading A either way. The packed B is the only scratch
-  // of these products: a call being captured, and one that finds no memory for
-  // it, take the kernels that need none.
-  const bool outweighs = M * N * K >= kSplitMinWork || (N > 128 && K >= 96 && M >= 256);
+  // columns, and of more than 64 from a size on (us, the tiles here -> three
+  // parts: A B 1,000 x 256 x 100 16.3 -> 12.1, x 256 33 -> 19; 30,000 x 128 x 256 28 ->
+  // 22; 3,000 x 128 x 256 19.6 -> 19.5, x 100 x 64 8.4 -> 12.2; A B^T, whose tiles
+  // load both operands along K, 1,000 x 256 x 100 10.0 -> 11.5, 8,192 x 256 x 256
+  // 18.4 -> 18.9), and every unaligned one that is not tiny (the general kernel
+  // loads element by element: 500,000 x 47 x 256 418 us, 170). Narrower aligned
+  // outputs are bound by reading A either way.
+  const bool outweighs = M * N * K >= kSplitMinWork ||
+                         (N > 128 && K >= (op == GCN_GEMM_NN ? 96 : 257) && M >= 256);
   if ((vec ? N > 64 && outweighs : M >= kSplitMinRows) &&
-      gemm_split_tall_takes(M, N, K, lda, ldc, mask ? ldm : 0) && !stream_capturing(stream)) {
-    const gcn_status st =
-        gemm_split_tall(op, M, N, K, A, lda, B, ldb, C, ldc, mask, ldm, relu, stream);
-    if (st != GCN_ENOMEM) return st;
-    clear_error();
-  }
+      gemm_split_tall_takes(op, M, N, K, lda, ldb, ldc, mask ? ldm : 0))
+    return gemm_split_tall(op, M, N, K, A, lda, B, ldb, C, ldc, mask, ldm, relu, stream);
   const dim3 grid((unsigned)ceil_div(M, kTile), (unsigned)ceil_div(N, kTile));
   ProfScope ps(op == GCN_GEMM_NN ? "gemm_nn" : "gemm_nt", stream);
   if (vec && op == GCN_GEMM_NN)

@@ -133,34 +133,6 @@ __device__ inline int result_row(int e, int lane) {
   return (e & 3) + 8 * (e >> 2) + 4 * (lane >> 5);
 }
 
-// ---- packed weights -------------------------------------------------------------
-
-// The parts of B (K x N, or its transpose stored N x K) in operand order:
-// block (kb, nb, part) of 32 columns x 16 k is 1 KB, 16 bytes per lane; zeros past
-// K and N. One thread per (block, lane).
-template <bool NT>
-__global__ __launch_bounds__(kThreads) void k_pack_split(int64_t N, int64_t K, int64_t nbt,
-                                                         int64_t kbt, const float* __restrict__ B,
-                                                         int64_t ldb, u4* __restrict__ bp) {
-  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int lane = (int)(t & 63);
-  const int64_t blk = t >> 6;
-  if (blk >= nbt * kbt) return;
-  const int64_t n = (blk % nbt) * 32 + (lane & 31);
-  const int64_t k0 = (blk / nbt) * 16 + 8 * (lane >> 5);
-  float x[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int64_t k = k0 + j;
-    x[j] = n < N && k < K ? (NT ? B[n * ldb + k] : B[k * ldb + n]) : 0.f;
-    if (n & 1) x[j] = -x[j];
-  }
-  u4 p[3];
-  split8(x, p);
-#pragma unroll
-  for (int s = 0; s < 3; ++s) bp[(blk * 3 + s) * 64 + lane] = p[s];
-}
-
 // ---- C = A B, A tall -------------------------------------------------------------
 
 struct TallArgs {
@@ -168,12 +140,9 @@ struct TallArgs {
   int N, K;
   const float* A;
   int64_t lda;
-  const u4* bp;   // k_pack_split of B, nbt column blocks
-  int nbt;
-  int col_tiles;
-  const float* B;  // B itself, for the tiles computed again
+  const float* B;
   int64_t ldb;
-  bool nt;
+  int col_tiles;
   float* C;
   int64_t ldc;
   const float* mask;
@@ -187,31 +156,42 @@ __device__ inline float finish(const TallArgs& a, float v, int64_t gm, int64_t g
 }
 
 // The 32 RBW x 32 NBW tile at (m0, n0) with fp32 multiply-adds.
-__device__ inline void tall_again(const TallArgs& a, int64_t m0, int64_t n0,
-                                                     int rows, int cols) {
+// A uniform pointer plus the lane's 32-bit offset in bytes (one scalar and one
+// vector register of address).
+__device__ inline const float* at_bytes(const float* base, uint32_t off) {
+  return reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + off);
+}
+
+template <bool BT>
+__device__ inline void tall_again(const TallArgs& a, int64_t m0, int64_t n0, int rows, int cols) {
   for (int i = threadIdx.x & 63; i < rows * cols; i += 64) {
     const int64_t gm = m0 + i / cols, gn = n0 + i % cols;
     if (gm >= a.M || gn >= a.N) continue;
     float s = 0.f;
     for (int k = 0; k < a.K; ++k)
       s = __builtin_fmaf(a.A[gm * a.lda + k],
-                         a.nt ? a.B[gn * a.ldb + k] : a.B[(int64_t)k * a.ldb + gn], s);
+                         BT ? a.B[gn * a.ldb + k] : a.B[(int64_t)k * a.ldb + gn], s);
     a.C[gm * a.ldc + gn] = finish(a, s, gm, gn);
   }
 }
 
 // WR x WC wavefronts, each with RBW x NBW blocks of 32 x 32 of C. A step
-// covers 16 of K: the workgroup's rows of A are loaded, split and laid out in
-// LDS in operand order, the packed B blocks are copied beside them, and the
-// next step's loads are in flight meanwhile (two LDS buffers, one barrier a step).
-template <int WR, int WC, int RBW, int NBW>
+// covers 16 of K: the workgroup's rows of A and columns of B are loaded, split
+// and laid out in LDS in operand order, and the next step's loads are in flight
+// meanwhile (two LDS buffers, one barrier a step). B is split by every
+// workgroup anew: laid out once by a kernel of its own it needed scratch, which a
+// captured call and one without free memory cannot have. BT: B is stored N x K.
+template <int WR, int WC, int RBW, int NBW, bool BT>
 __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
   constexpr int RB = WR * RBW, NB = WC * NBW;  // blocks of the workgroup's tile
   constexpr int ROWS = RB * 32;
   constexpr int NT = 64 * WR * WC, RP = NT / 4;  // threads; rows of A loaded at a time
-  constexpr int AP = ROWS * 4 / NT;                      // 16-byte pieces of A per thread
-  constexpr int BP = (NB * 3 * 64 + NT - 1) / NT;  // 16-byte pieces of B per thread
-  constexpr bool BFULL = NB * 3 * 64 % NT == 0;
+  constexpr int AP = ROWS * 4 / NT;  // 16-byte pieces of A per thread
+  // of B, 16-byte pieces like A's, or units of 8 rows (4 where those do not fill
+  // the threads: 192 columns 1.49 ms instead of 1.67) of one column
+  constexpr int BV = BT || (NB * 64 % NT != 0 && NB * 128 % NT == 0) ? 4 : 8;
+  constexpr int BUNITS = NB * 512 / BV, BP = (BUNITS + NT - 1) / NT;
+  constexpr bool BFULL = BUNITS % NT == 0;
   __shared__ __align__(16) char lds[2][(RB + NB) * 3 * kFrag];
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wr = w / WC, wc = w % WC;
@@ -220,7 +200,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
   const int64_t xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
   const int ct = (int)(idx % a.col_tiles);
   const int64_t m0 = ((idx / a.col_tiles) * 8 + xcd) * ROWS;
-  const int nb0 = ct * NB;
+  const int n0 = ct * NB * 32;
   if (m0 >= a.M) return;  // the whole workgroup
 
   // a thread's pieces of A: row t / 4 + RP p, k = 4 (t % 4) .. + 3
@@ -229,52 +209,106 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
 #pragma unroll
   for (int p = 0; p < AP; ++p) {
     const int r = (t >> 2) + RP * p;
-    ao[p] = (uint32_t)(m0 + r < a.M ? r : (int)(a.M - 1 - m0)) * (uint32_t)a.lda + 4 * (t & 3);
+    ao[p] = 4 * ((uint32_t)(m0 + r < a.M ? r : (int)(a.M - 1 - m0)) * (uint32_t)a.lda + 4 * (t & 3));
   }
   const float sign = (t >> 2) & 1 ? -1.f : 1.f;
-  const u4* bp = a.bp + (int64_t)nb0 * 3 * 64;
-  const int64_t bstep = (int64_t)a.nbt * 3 * 64;
-  // where its pieces go: block row / 32, lane row % 32 + 32 (k / 8), half k / 4 % 2
+  // of B: as of A, or unit u: block u / (512 / BV), column u % 32 of it,
+  // k = BV (u / 32 % (16 / BV)) .. + BV - 1
+  const int bk = BT ? 4 * (t & 3) : BV * ((t >> 5) & (16 / BV - 1));
+  const float* bt = BT ? a.B + n0 * a.ldb : a.B + n0;
+  uint32_t bo[BP];
+#pragma unroll
+  for (int p = 0; p < BP; ++p) {
+    const int u = t + NT * p;
+    const int c = BT ? (t >> 2) + RP * p : u / (512 / BV) * 32 + (u & 31);
+    const uint32_t in = (uint32_t)(n0 + c < a.N ? c : a.N - 1 - n0);
+    bo[p] = 4 * (BT ? in * (uint32_t)a.ldb + bk : in + (uint32_t)bk * (uint32_t)a.ldb);
+  }
+  const float bsign = BT ? sign : (t & 1 ? -1.f : 1.f);
+  // where the 16-byte pieces go: block row / 32, lane row % 32 + 32 (k / 8), half k / 4 % 2
   const int a_off = (t >> 7) * 3 * kFrag + ((t >> 2) & 31) * 16 + ((t >> 1) & 1) * 512 + (t & 1) * 8;
 
   const int steps = (a.K + kKs - 1) / kKs;
   f4u av[2][AP];  // A of the next step and of the one after it
-  u4 bv[BP];
+  float bv[BP][BV];
   auto load_a = [&](f4u* v, int ks) {
     const int k0 = ks * kKs, k = k0 + 4 * (t & 3);
     if (k0 + kKs <= a.K) {
 #pragma unroll
-      for (int p = 0; p < AP; ++p) v[p] = *reinterpret_cast<const f4u*>((at + k0) + ao[p]);
+      for (int p = 0; p < AP; ++p) v[p] = *reinterpret_cast<const f4u*>(at_bytes(at + k0, ao[p]));
     } else {  // the last, partial step, and the steps past it (not used)
 #pragma unroll
       for (int p = 0; p < AP; ++p)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[p][j] = k + j < a.K ? (at + k0)[ao[p] + j] : 0.f;
+        for (int j = 0; j < 4; ++j) v[p][j] = k + j < a.K ? at_bytes(at + k0, ao[p])[j] : 0.f;
     }
   };
   auto load_b = [&](int ks) {
-    const u4* q = bp + (ks < steps ? ks : steps - 1) * bstep;
+    const int k0 = ks * kKs;
+    const bool full = k0 + kKs <= a.K;  // else the last, partial step, or one past it
 #pragma unroll
-    for (int p = 0; p < BP; ++p)
-      if (BFULL || t + p * NT < NB * 3 * 64) bv[p] = q[(uint32_t)t + p * NT];
+    for (int p = 0; p < BP; ++p) {
+      if (!BFULL && t + p * NT >= BUNITS) continue;
+      if constexpr (BT) {
+        const float* q = at_bytes(bt + k0, bo[p]);
+        if (full) {
+          const f4u v = *reinterpret_cast<const f4u*>(q);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) bv[p][j] = v[j];
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) bv[p][j] = k0 + bk + j < a.K ? q[j] : 0.f;
+        }
+      } else {
+        const float* q = bt + (int64_t)k0 * a.ldb;
+        if (full) {
+#pragma unroll
+          for (int j = 0; j < BV; ++j) bv[p][j] = *at_bytes(q + j * a.ldb, bo[p]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < BV; ++j)
+            bv[p][j] = k0 + bk + j < a.K ? *at_bytes(q + j * a.ldb, bo[p]) : 0.f;
+        }
+      }
+    }
+  };
+  auto store4 = [](char* q, float x0, float x1, float x2, float x3) {
+    uint32_t h0, m0, l0, h1, m1, l1;
+    split2(x0, x1, h0, m0, l0);
+    split2(x2, x3, h1, m1, l1);
+    *reinterpret_cast<u2*>(q) = u2{h0, h1};
+    *reinterpret_cast<u2*>(q + kFrag) = u2{m0, m1};
+    *reinterpret_cast<u2*>(q + 2 * kFrag) = u2{l0, l1};
   };
   auto store_a = [&](char* buf, const f4u* v) {
 #pragma unroll
-    for (int p = 0; p < AP; ++p) {
-      uint32_t h0, m0, l0, h1, m1, l1;
-      split2(v[p][0] * sign, v[p][1] * sign, h0, m0, l0);
-      split2(v[p][2] * sign, v[p][3] * sign, h1, m1, l1);
-      char* q = buf + RP / 32 * p * 3 * kFrag + a_off;
-      *reinterpret_cast<u2*>(q) = u2{h0, h1};
-      *reinterpret_cast<u2*>(q + kFrag) = u2{m0, m1};
-      *reinterpret_cast<u2*>(q + 2 * kFrag) = u2{l0, l1};
-    }
+    for (int p = 0; p < AP; ++p)
+      store4(buf + RP / 32 * p * 3 * kFrag + a_off, v[p][0] * sign, v[p][1] * sign, v[p][2] * sign,
+             v[p][3] * sign);
   };
   auto store_b = [&](char* buf) {
-    u4* q = reinterpret_cast<u4*>(buf + RB * 3 * kFrag) + t;
+    buf += RB * 3 * kFrag;
 #pragma unroll
-    for (int p = 0; p < BP; ++p)
-      if (BFULL || t + p * NT < NB * 3 * 64) q[p * NT] = bv[p];
+    for (int p = 0; p < BP; ++p) {
+      if (!BFULL && t + p * NT >= BUNITS) continue;
+      const int u = t + p * NT;
+#pragma unroll
+      for (int j = 0; j < BV; ++j) bv[p][j] *= bsign;
+      if constexpr (BT) {
+        store4(buf + RP / 32 * p * 3 * kFrag + a_off, bv[p][0], bv[p][1], bv[p][2], bv[p][3]);
+      } else if constexpr (BV == 4) {
+        const int r = (t >> 5) & 3;  // its quarter of the step
+        store4(buf + (u >> 7) * 3 * kFrag + ((t & 31) + 32 * (r >> 1)) * 16 + (r & 1) * 8, bv[p][0],
+               bv[p][1], bv[p][2], bv[p][3]);
+      } else {
+        u4 s[3];
+        split8(bv[p], s);
+        u4* q = reinterpret_cast<u4*>(buf) + (u >> 6) * 3 * 64 + (u & 63);
+        q[0] = s[0];
+        q[64] = s[1];
+        q[128] = s[2];
+      }
+    }
   };
 
   f16 acc[RBW][NBW];
@@ -312,7 +346,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
   if (ks < steps) step(ks, lds[0], lds[1], av[1], av[0]);
 
   const int64_t wm = m0 + wr * RBW * 32;
-  const int wn = (nb0 + wc * NBW) * 32;
+  const int wn = n0 + wc * NBW * 32;
   const float csign = lane & 1 ? -1.f : 1.f;
   float bad = 0.f;  // NaN once a sum is not finite
   if (wm + RBW * 32 <= a.M && wn + NBW * 32 <= a.N) {
@@ -352,7 +386,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
         }
       }
   }
-  if (__any(bad != bad)) tall_again(a, wm, wn, RBW * 32, NBW * 32);
+  if (__any(bad != bad)) tall_again<BT>(a, wm, wn, RBW * 32, NBW * 32);
 }
 
 // ---- C = A^T B, K = rows in the millions ---------------------------------------------
@@ -518,20 +552,46 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
 
 // ---- launch ----------------------------------------------------------------------
 
-// The lane parts of the addresses are 32-bit byte offsets over the rows of a
-// tile (256 of A, 4 of C; 8 of A and B in A^T B); larger strides, and sizes
-// beyond 2^30, stay with the general kernels.
-bool gemm_split_tall_takes(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldc,
-                           int64_t ldm) {
+// The lane parts of the addresses are 32-bit offsets over the rows of a tile
+// (256 of A and of B stored N x K, 8 of B stored K x N and of both operands of
+// A^T B, 4 of C); larger strides, and sizes beyond 2^30, stay with the general
+// kernels.
+bool gemm_split_tall_takes(int op, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                           int64_t ldc, int64_t ldm) {
   return M < (int64_t(1) << 33) && N < (int64_t(1) << 30) && K >= 16 && K <= 4096 &&
-         N * K < (int64_t(1) << 34) &&  // a thread per 8 elements of the packed B
-         lda < (int64_t(1) << 22) && ldc < (int64_t(1) << 27) && ldm < (int64_t(1) << 27);
+         lda < (int64_t(1) << 22) && ldb < (int64_t(1) << (op == GCN_GEMM_NT ? 22 : 26)) &&
+         ldc < (int64_t(1) << 27) && ldm < (int64_t(1) << 27);
 }
 
 bool gemm_split_tn_takes(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
   return M < (int64_t(1) << 30) && N < (int64_t(1) << 30) && K >= 64 &&
          lda < (int64_t(1) << 26) && ldb < (int64_t(1) << 26);
 }
+
+namespace {
+
+template <bool BT>
+hipError_t launch_split_tall(const TallArgs& a, int per, hipStream_t stream) {
+  auto go = [&](auto kern, int threads, int64_t rows) {
+    const int64_t row_tiles = ceil_div(ceil_div(a.M, rows), (int64_t)8) * 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(row_tiles * a.col_tiles)), dim3(threads), 0, stream,
+                       a);
+    return hipGetLastError();
+  };
+  // 256 columns: 256-row tiles of eight wavefronts, which split B half as often,
+  // once there are tiles for most CUs; below that 64 rows.
+  switch (per) {
+    case 1: return go(k_split_tall<4, 1, 1, 1, BT>, 256, 128);
+    case 2: return go(k_split_tall<4, 1, 1, 2, BT>, 256, 128);
+    case 4: return go(k_split_tall<2, 2, 2, 2, BT>, 256, 128);
+    case 6: return go(k_split_tall<2, 2, 2, 3, BT>, 256, 128);
+    default:
+      return a.M >= 32768 ? go(k_split_tall<4, 2, 2, 4, BT>, 512, 256)
+                          : go(k_split_tall<1, 4, 2, 2, BT>, 256, 64);
+  }
+}
+
+}  // namespace
 
 gcn_status gemm_split_tall(int op, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                            const float* B, int64_t ldb, float* C, int64_t ldc, const float* mask,
@@ -541,42 +601,10 @@ gcn_status gemm_split_tall(int op, int64_t M, int64_t N, int64_t K, const float*
   const int64_t col_tiles = ceil_div(nb, (int64_t)8);
   int per = (int)ceil_div(nb, col_tiles);
   per = per <= 2 ? per : (per + 1) / 2 * 2;
-  const int64_t nbt = per * col_tiles, kbt = ceil_div(K, (int64_t)kKs);
-  u4* bp = nullptr;
-  GCN_CHECK(talloc(&bp, nbt * kbt * 3 * 64, stream, "packed weights"));
   ProfScope ps(op == GCN_GEMM_NN ? "gemm_nn" : "gemm_nt", stream);
-  const dim3 pgrid((unsigned)ceil_div(nbt * kbt * 64, (int64_t)kThreads));
-  if (op == GCN_GEMM_NN)
-    hipLaunchKernelGGL(k_pack_split<false>, pgrid, dim3(kThreads), 0, stream, N, K, nbt, kbt, B,
-                       ldb, bp);
-  else
-    hipLaunchKernelGGL(k_pack_split<true>, pgrid, dim3(kThreads), 0, stream, N, K, nbt, kbt, B,
-                       ldb, bp);
-  hipError_t e = hipGetLastError();
-  const TallArgs a{M,   (int)N, (int)K, A, lda, bp,   (int)nbt, (int)col_tiles, B,
-                   ldb, op == GCN_GEMM_NT, C, ldc, mask, ldm, relu};
-  auto go = [&](auto kern, int threads, int64_t rows) {
-    const int64_t row_tiles = ceil_div(ceil_div(M, rows), (int64_t)8) * 8;
-    if (e != hipSuccess) return;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(row_tiles * col_tiles)), dim3(threads), 0, stream, a);
-    e = hipGetLastError();
-  };
-  // 256 columns: 256-row tiles of eight wavefronts, which read the packed B
-  // half as often (2.45M x 256 x 516: 3.61 ms against 3.66 with 128 rows),
-  // once there are tiles for most CUs; below that 64 rows (16,384 x 256 x
-  // 516: 45 us against 60 with 128 rows and 77 with 256).
-  switch (per) {
-    case 1: go(k_split_tall<4, 1, 1, 1>, 256, 128); break;
-    case 2: go(k_split_tall<4, 1, 1, 2>, 256, 128); break;
-    case 4: go(k_split_tall<2, 2, 2, 2>, 256, 128); break;
-    case 6: go(k_split_tall<2, 2, 2, 3>, 256, 128); break;
-    default:
-      if (M >= 32768)
-        go(k_split_tall<4, 2, 2, 4>, 512, 256);
-      else
-        go(k_split_tall<1, 4, 2, 2>, 256, 64);
-  }
-  tfree(bp, stream);
+  const TallArgs a{M, (int)N, (int)K, A, lda, B, ldb, (int)col_tiles, C, ldc, mask, ldm, relu};
+  const hipError_t e = op == GCN_GEMM_NN ? launch_split_tall<false>(a, per, stream)
+                                         : launch_split_tall<true>(a, per, stream);
   if (e != hipSuccess) return hip_fail(e, "k_split_tall", __FILE__, __LINE__);
   return GCN_OK;
 }

@@ -148,3 +148,51 @@ def test_captured(G, op, M, N, K):
         want, scale = _pair(A, B)
         assert_close(host(Cd), want, scale, what="replay %d" % rep)
         assert_close(eager, want, scale, what="eager %d" % rep)
+
+
+@pytest.mark.parametrize("op,M,N,K", [("NN", 4097, 47, 100), ("NN", 40000, 256, 101),
+                                      ("NN", 5000, 192, 516), ("NT", 40000, 200, 128),
+                                      ("NT", 4100, 161, 47)])
+def test_captured_bits(G, op, M, N, K):
+    """A captured product is the eager one, bit for bit."""
+    import torch
+    note("split captured bits %s %s" % (op, (M, N, K)))
+    code = G.GCN_GEMM_NN if op == "NN" else G.GCN_GEMM_NT
+    Ad = torch.zeros((M, K), device="cuda:0")
+    Bd = dev(synth.uniform(341, K, N) if op == "NN" else synth.uniform(341, N, K))
+    Cd = torch.empty((M, N), device="cuda:0")
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()  # default priority
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        G.gcn_gemm_f32(code, Ad, Bd, C=Cd)
+    torch.cuda.synchronize()
+    for rep in range(3):
+        Ad.copy_(dev(synth.uniform(342 + rep, M, K)))
+        Cd.fill_(7.0)  # eager work between the replays
+        eager = G.gcn_gemm_f32(code, Ad, Bd)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(eager.view(torch.int32), Cd.view(torch.int32))
+
+
+# B is split by every workgroup: its units over the threads of each tile width,
+# rows and columns past its edges, both ways it can be stored
+@pytest.mark.parametrize("M,N,K", [(4096, 31, 16), (4099, 63, 18), (4096, 128, 33), (4100, 191, 31),
+                                   (4100, 193, 47), (33000, 225, 30), (40000, 449, 65)])
+def test_b_edges(G, M, N, K):
+    import torch
+    note("split B edges %dx%dx%d" % (M, N, K))
+    A, B = synth.uniform(351, M, K + 1)[:, :K], synth.uniform(352, K, N)
+    ref, S = _pair(A, B)
+    for ld in (N, N + 5):  # rows of B, then of its transpose, inside wider ones
+        Bp = torch.full((K, ld), float("nan"), device="cuda:0")
+        Bp[:, :N] = dev(B)
+        out = G.gcn_gemm_f32(G.GCN_GEMM_NN, dev(np.ascontiguousarray(A)), Bp[:, :N])
+        assert_close(host(out), ref, S, what="NN")
+        Bt = torch.full((N, K + ld - N), float("nan"), device="cuda:0")
+        Bt[:, :K] = dev(np.ascontiguousarray(B.T))
+        out = G.gcn_gemm_f32(G.GCN_GEMM_NT, dev(np.ascontiguousarray(A)), Bt[:, :K])
+        assert_close(host(out), ref, S, what="NT")
