@@ -196,3 +196,60 @@ def test_b_edges(G, M, N, K):
         Bt[:, :K] = dev(np.ascontiguousarray(B.T))
         out = G.gcn_gemm_f32(G.GCN_GEMM_NT, dev(np.ascontiguousarray(A)), Bt[:, :K])
         assert_close(host(out), ref, S, what="NT")
+
+
+# the tiles of every width, at their edges and inside, with a sum that is not
+# finite: that tile is computed again, the others are not touched
+@pytest.mark.parametrize("op,M,N,K", [("NN", 4100, 31, 19), ("NN", 4100, 64, 37), ("NN", 4100, 127, 40),
+                                      ("NN", 33000, 192, 50), ("NN", 33000, 256, 96), ("NN", 5000, 255, 111),
+                                      ("NT", 4100, 97, 36), ("NT", 33000, 256, 101), ("NT", 5000, 250, 259),
+                                      ("TN", 300, 257, 131079), ("TN", 100, 100, 7003), ("TN", 40, 33, 2001),
+                                      ("TN", 40, 20, 2001)])
+def test_not_finite_tiles(G, op, M, N, K):
+    import torch
+    note("split not finite %s %s" % (op, (M, N, K)))
+    gen = torch.Generator(device="cuda:0").manual_seed(360)
+    A = torch.randn(M, K, device="cuda:0", generator=gen)
+    B = torch.randn(K, N, device="cuda:0", generator=gen)
+    ref, S = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+    rows = {0: float("inf"), M // 2: float("nan"), M - 1: float("-inf")}
+    for r, v in rows.items():
+        A[r, K // 3] = v
+    B[K // 3, N - 1] = 0.0
+    if op == "TN":
+        C = G.gcn_gemm_f32(G.GCN_GEMM_TN, A.t().contiguous(), B)
+    elif op == "NT":
+        C = G.gcn_gemm_f32(G.GCN_GEMM_NT, A, B.t().contiguous())
+    else:
+        C = G.gcn_gemm_f32(G.GCN_GEMM_NN, A, B)
+    for r, v in rows.items():
+        want = v * B[K // 3]  # infinities of either sign, NaN where B is 0
+        assert torch.equal(torch.isnan(C[r]), torch.isnan(want))
+        assert torch.equal(C[r].nan_to_num(nan=7.0), want.nan_to_num(nan=7.0))
+    keep = torch.ones(M, dtype=torch.bool, device="cuda:0")
+    keep[list(rows)] = False
+    keep = keep[:, None] & (torch.arange(N, device="cuda:0") < N - 1)
+    assert torch.all(((C.double() - ref).abs() <= 1e-5 * S)[keep])
+
+
+def test_not_finite_time(G):
+    """A diverged run's products take a few times as long, not a hundred (3.6
+    times measured, 100 when the tiles were computed again element by element)."""
+    import torch
+    note("split not finite, time")
+    A = torch.randn(32768, 516, device="cuda:0")
+    B = torch.randn(516, 256, device="cuda:0")
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+
+    def ms():
+        best = float("inf")
+        for _ in range(6):
+            a.record()
+            G.gcn_gemm_f32(G.GCN_GEMM_NN, A, B)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+    finite = ms()
+    A.fill_(float("nan"))
+    assert ms() < 20 * finite
