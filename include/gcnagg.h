@@ -212,7 +212,7 @@ enum { GCN_GEMM_NN = 0, GCN_GEMM_NT = 1, GCN_GEMM_TN = 2 };
  * lda, ldb, ldc are the row strides of the stored matrices. fp32 inputs and
  * fp32 accumulation; large products split each input exactly into three bf16
  * parts and add six of the nine products of the parts (the three left out are
- * below 2^-26 of the largest). */
+ * at most about 2^-24 of the product, one fp32 rounding). */
 gcn_status gcn_gemm_f32(int op, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda,
                         const float* B, int64_t ldb, float* C, int64_t ldc, void* stream);
 

@@ -9,13 +9,22 @@
 // Precision. An fp32 number has 24 significant bits; h = bf16(x), m =
 // bf16(x - h), l = bf16(x - h - m), each rounded to nearest even, hold 8 of
 // them each, and both differences are exact, so h + m + l = x. With |m| <=
-// 2^-9 |h| and |l| <= 2^-18 |h| the products left out (m l, l m, l l) are below
-// 2^-26 of h h, a quarter of an fp32 rounding. The six others are exact in
-// the matrix core and are added to the fp32 accumulator sixteen at a time, the
-// small ones first. Against 64 bits, normal values, K = 100 / 256 / 516:
+// 2^-8 |h| and |l| <= 2^-17 |h| the products left out (m l, l m, l l) are below
+// 2^-24 of h h by no more than a 2^-10th, an fp32 rounding where the operands
+// are the worst ones (1.0038834 squared) and far below it on average. The six others are
+// exact in the matrix core and are added to the fp32 accumulator sixteen at a time,
+// the small ones first. Against 64 bits, normal values, K = 100 / 256 / 516:
 // 1.5e-7 / 2.4e-7 / 3.5e-7 here, 1.8e-7 / 2.9e-7 / 4.1e-7 with
-// v_mfma_f32_16x16x4_f32. (Operands below 2^-109 lose low bits of l to bf16's
-// smallest exponent.)
+// v_mfma_f32_16x16x4_f32; all operands 1.0038834, K = 16 / 256 / 1024: 5.9e-8 /
+// 1.8e-7 / 1.8e-7 and 5.9e-8 / 5.9e-8 / 1.5e-5.
+//
+// Small operands. The parts of an fp32 number are multiples of 2^-149, its
+// smallest step, but a bf16 part below 2^-126 counts as 0 in the matrix core. So
+// both operands are taken times 2^24 (with the signs below, in the same
+// multiplication), which makes every part 0 or at least 2^-125, and the sums
+// times 2^-48. Operands from 2^104 on, and sums from 2^80, then leave the range
+// and take the route of the infinities. (Not scaled, operands about 2^-118 lost m's
+// low bits and products were off by 8.8e-6, about 2^-124 by 5.6e-4.)
 //
 // The matrix core rounds the aligned products towards minus infinity some 8 bits
 // below the sum's last bit. That bias is far below a rounding, but it has the same
@@ -27,8 +36,8 @@
 //
 // Infinities, NaN and operands that round up to infinity give a NaN in the
 // sums of the parts, whatever the fp32 product would be; a wavefront whose
-// tile holds a sum that is not finite therefore computes that tile again with
-// fp32 multiply-adds.
+// tile holds a sum that is not finite therefore computes that tile again on the
+// fp32 matrix instruction.
 //
 // What bounds them: random operands hold the chip's bf16 matrix cores at about 1.1
 // PFLOP/s (an 8192^3 library product reaches 1.12), 185 TFLOP/s of fp32
@@ -56,6 +65,7 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 constexpr int kThreads = 256;  // four wavefronts
 constexpr int kKs = 16;        // K of one step: one matrix instruction deep
 constexpr int kFrag = 1024;    // bytes of one 32 x 16 operand block of one part
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;  // of an operand, of a sum
 
 // The parts of two neighbouring values, each pair packed in 32 bits.
 __device__ inline void split2(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
@@ -238,7 +248,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
     const int r = (t >> 2) + RP * p;
     ao[p] = 4 * ((uint32_t)(m0 + r < a.M ? r : (int)(a.M - 1 - m0)) * (uint32_t)a.lda + 4 * (t & 3));
   }
-  const float sign = (t >> 2) & 1 ? -1.f : 1.f;
+  const float sign = (t >> 2) & 1 ? -kUp : kUp;
   // of B: as of A, or unit u: block u / (512 / BV), column u % 32 of it,
   // k = BV (u / 32 % (16 / BV)) .. + BV - 1
   const int bk = BT ? 4 * (t & 3) : BV * ((t >> 5) & (16 / BV - 1));
@@ -251,7 +261,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
     const uint32_t in = (uint32_t)(n0 + c < a.N ? c : a.N - 1 - n0);
     bo[p] = 4 * (BT ? in * (uint32_t)a.ldb + bk : in + (uint32_t)bk * (uint32_t)a.ldb);
   }
-  const float bsign = BT ? sign : (t & 1 ? -1.f : 1.f);
+  const float bsign = BT ? sign : (t & 1 ? -kUp : kUp);
   // where the 16-byte pieces go: block row / 32, lane row % 32 + 32 (k / 8), half k / 4 % 2
   const int a_off = (t >> 7) * 3 * kFrag + ((t >> 2) & 31) * 16 + ((t >> 1) & 1) * 512 + (t & 1) * 8;
 
@@ -374,8 +384,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
 
   const int64_t wm = m0 + wr * RBW * 32;
   const int wn = n0 + wc * NBW * 32;
-  // the signs of even and odd rows in the lane's column
-  float even = lane & 1 ? -1.f : 1.f, odd = -even;
+  // the signs and scale of even and odd rows in the lane's column
+  float even = lane & 1 ? -kDown : kDown, odd = -even;
   if (not_finite<RBW, NBW>(acc)) {
     even = odd = 1.f;
     auto load = [&](int64_t k, float (*x)[4], float (*y)[4]) {
@@ -482,7 +492,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
     bo[p] = (uint32_t)(8 * ((u >> 5) & 1)) * (uint32_t)a.ldb + ((c < a.N ? c : a.N - 1) - n0);
   }
   const int h8 = 8 * ((t >> 5) & 1);  // the half is the same for all of a thread's units
-  float sign = chunk & 1 ? -1.f : 1.f;
+  const float sign = chunk & 1 ? -kUp : kUp;
+  float down = chunk & 1 ? -kDown : kDown;
   struct Pieces {
     float a[AU][8], b[BU][8];
   } v[PF];
@@ -523,6 +534,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
     for (int p = 0; p < BU; ++p) {
       const int u = t + p * NT;
       u4 s[3];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v.b[p][j] *= kUp;
       split8(v.b[p], s);
       u4* q = reinterpret_cast<u4*>(buf + RB * 3 * kFrag) + (u >> 6) * 3 * 64 + (u & 63);
       if (NB * 64 % NT == 0 || u < NB * 64) { q[0] = s[0]; q[64] = s[1]; q[128] = s[2]; }
@@ -560,7 +573,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
   float* part = a.part + chunk * a.M * a.N;
   const int wm = m0 + wr * RBW * 32, wn = n0 + wc * NBW * 32;
   if (not_finite<RBW, NBW>(acc)) {
-    sign = 1.f;
+    down = 1.f;
     auto load = [&](int64_t k, float (*x)[4], float (*y)[4]) {
 #pragma unroll
       for (int i = 0; i < RBW; ++i) {
@@ -587,7 +600,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int m = wm + i * 32 + result_row(e, lane);
-        if (m < a.M && n < a.N) part[(int64_t)m * a.N + n] = acc[i][j][e] * sign;
+        if (m < a.M && n < a.N) part[(int64_t)m * a.N + n] = acc[i][j][e] * down;
       }
     }
 }

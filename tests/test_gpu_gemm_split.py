@@ -253,3 +253,51 @@ def test_not_finite_time(G):
     finite = ms()
     A.fill_(float("nan"))
     assert ms() < 20 * finite
+
+
+# fp32 holds 24 bits of a number down to 2^-126 and fewer below; so do the parts.
+# Rounding errors of either sign leave 2.4e-7 here (2.9e-7 on the fp32
+# instruction, which takes the largest numbers); four times that.
+@pytest.mark.parametrize("ea,eb", [(0, 0), (-100, 20), (-112, 20), (-118, 20), (-124, 20), (-130, 20),
+                                   (-140, 30), (20, -124), (60, -118), (-60, -55), (100, -60),
+                                   (112, -100), (60, 40), (-100, 110)])
+@pytest.mark.parametrize("op", ["NN", "NT", "TN"])
+def test_range(G, op, ea, eb):
+    import torch
+    note("split operands of 2^%d and 2^%d, %s" % (ea, eb, op))
+    gen = torch.Generator(device="cuda:0").manual_seed(370)
+    M, N, K = (8000, 256, 256) if op != "TN" else (256, 128, 5000)
+    A = torch.randn(M, K, device="cuda:0", generator=gen).double().mul(2.0 ** ea).float()
+    B = torch.randn(K, N, device="cuda:0", generator=gen).double().mul(2.0 ** eb).float()
+    ref = A.double() @ B.double()
+    if op == "TN":
+        C = G.gcn_gemm_f32(G.GCN_GEMM_TN, A.t().contiguous(), B)
+    elif op == "NT":
+        C = G.gcn_gemm_f32(G.GCN_GEMM_NT, A, B.t().contiguous())
+    else:
+        C = G.gcn_gemm_f32(G.GCN_GEMM_NN, A, B)
+    rel = ((C.double() - ref).norm() / ref.norm()).item()
+    note("rel %.2e" % rel)
+    assert rel <= 1.2e-6
+
+
+@pytest.mark.parametrize("K", [16, 100, 256, 1024])
+def test_worst_operands(G, K):
+    """All operands 1.0038834: the products left out are 2^-24 of each product,
+    all of one sign. Beyond that a rounding per 16 of each of six products, at
+    most 2^-24 of the sum each."""
+    import torch
+    note("split worst operands K=%d" % K)
+    v = 1.0038834
+    A = torch.full((32768, K), v, device="cuda:0")
+    B = torch.full((K, 256), v, device="cuda:0")
+    want = A[0, 0].double().item() ** 2
+    bound = (1.001 + 6 * -(-K // 16)) * 2.0 ** -24
+    nn = G.gcn_gemm_f32(G.GCN_GEMM_NN, A, B).double() / (want * K) - 1
+    nt = G.gcn_gemm_f32(G.GCN_GEMM_NT, A, B.t().contiguous()).double() / (want * K) - 1
+    note("NN %.2e NT %.2e" % (nn.abs().max(), nt.abs().max()))
+    assert nn.abs().max() <= bound and nt.abs().max() <= bound
+    A, B = torch.full((64 * K, 256), v, device="cuda:0"), torch.full((64 * K, 128), v, device="cuda:0")
+    tn = G.gcn_gemm_f32(G.GCN_GEMM_TN, A, B).double() / (want * 64 * K) - 1
+    note("TN %.2e" % tn.abs().max())
+    assert tn.abs().max() <= (1.001 + 6 * 64 * K / 16) * 2.0 ** -24
