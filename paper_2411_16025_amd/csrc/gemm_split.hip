@@ -384,7 +384,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
 
   const int64_t wm = m0 + wr * RBW * 32;
   const int wn = n0 + wc * NBW * 32;
-  // the signs and scale of even and odd rows in the lane's column
+  // the signs and scale of even and odd rows in the lane's column (with 0 added
+  // to the product: -0 becomes +0)
   float even = lane & 1 ? -kDown : kDown, odd = -even;
   if (not_finite<RBW, NBW>(acc)) {
     even = odd = 1.f;
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
         const float* mk = a.mask + (wm + i * 32 + result_row(e, 0)) * a.ldm + wn;
 #pragma unroll
         for (int j = 0; j < NBW; ++j) {
-          float v = acc[i][j][e] * (e & 1 ? odd : even);
+          float v = __builtin_fmaf(acc[i][j][e], e & 1 ? odd : even, 0.f);
           if (a.mask) v = mk[lm + j * 32] > 0.f ? v : 0.f;
           if (a.relu) v = fmaxf(v, 0.f);
           c[lc + j * 32] = v;
@@ -434,7 +435,8 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
         for (int e = 0; e < 16; ++e) {
           const int64_t gm = wm + i * 32 + result_row(e, lane);
           if (gm < a.M && gn < a.N)
-            a.C[gm * a.ldc + gn] = finish(a, acc[i][j][e] * (e & 1 ? odd : even), gm, gn);
+            a.C[gm * a.ldc + gn] =
+                finish(a, __builtin_fmaf(acc[i][j][e], e & 1 ? odd : even, 0.f), gm, gn);
         }
       }
   }

@@ -301,3 +301,23 @@ def test_worst_operands(G, K):
     tn = G.gcn_gemm_f32(G.GCN_GEMM_TN, A, B).double() / (want * 64 * K) - 1
     note("TN %.2e" % tn.abs().max())
     assert tn.abs().max() <= (1.001 + 6 * 64 * K / 16) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("op", ["NN", "NT", "TN"])
+def test_zero_sums_have_no_sign(G, op):
+    """Sums of exact zeros are +0, as on the fp32 instruction, also where they are
+    formed of negated products."""
+    import torch
+    note("split zeros %s" % op)
+    M, N, K = (8000, 256, 256) if op != "TN" else (256, 128, 5000)
+    A, B = torch.randn(M, K, device="cuda:0"), torch.randn(K, N, device="cuda:0")
+    A[::3] = 0.0
+    B[:, 5::7] = 0.0
+    if op == "TN":
+        C = G.gcn_gemm_f32(G.GCN_GEMM_TN, A.t().contiguous(), B)
+    elif op == "NT":
+        C = G.gcn_gemm_f32(G.GCN_GEMM_NT, A, B.t().contiguous())
+    else:
+        C = G.gcn_gemm_f32(G.GCN_GEMM_NN, A, B)
+    bits = C.view(torch.int32)
+    assert torch.all(bits[::3] == 0) and torch.all(bits[:, 5::7] == 0)
