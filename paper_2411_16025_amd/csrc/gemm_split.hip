@@ -677,19 +677,26 @@ gcn_status gemm_split_tn(int64_t M, int64_t N, int64_t K, const float* A, int64_
   const int64_t tm = wide ? 256 : 128;
   const int64_t tn = wide ? 256 : (N <= 32 ? 32 : (N <= 64 ? 64 : 128));
   const int64_t m_tiles = ceil_div(M, tm), n_tiles = ceil_div(N, tn), tiles = m_tiles * n_tiles;
-  // Rows of a chunk: at most those after which the sums are at least as close
-  // to 64 bits as the fp32 instruction's were (1024 of small outputs: 256 x
-  // 96 x 2.45M 6.5e-7 against 7.2e-7; 2048: 512 x 256 7.5e-7 against 11.7e-7),
-  // more for outputs whose partials would weigh more than the operands. A
-  // multiple of 512 workgroups, a fixed count so that the order of the sums
-  // does not depend on the device.
-  const int64_t rows = M * N <= 32768 ? 1024 : (M * N <= 262144 ? 2048 : 8192);
+  // Rows of a chunk: at most those after which the sums are as close to 64 bits as
+  // the fp32 instruction's were in chunks of `most` rows (1024, or more where C
+  // has many tiles and K many rows): 1408 rows here are like 1024 there (300 x 300
+  // x 500,000 in 1312 rows 5.9e-7 against 6.1e-7; in 1968 rows 7.0e-7). And 1024 for small
+  // outputs, 2048 for most, so that long sums stay below that (256 x 96 x 2.45M
+  // 6.5e-7 against 7.2e-7; 512 x 256 7.4e-7 against 11.7e-7). A multiple of 512
+  // workgroups, a fixed count so that the order of the sums does not depend on
+  // the device.
+  const int64_t fp32_tiles = ceil_div(M, (int64_t)128) * ceil_div(N, (int64_t)(N <= 64 ? 64 : 128));
+  int64_t most = 8192;
+  while (most > 1024 && fp32_tiles * ceil_div(K, most) < 4096) most /= 2;
+  const int64_t rows = std::min<int64_t>(
+      M * N <= 32768 ? 1024 : (M * N <= 262144 ? 2048 : 8192), most + most * 3 / 8);
   const int64_t rounds = std::max<int64_t>(1, ceil_div(K * tiles, (int64_t)512 * rows));
   const int64_t want = std::max<int64_t>(1, 512 * rounds / tiles);
   // Short sums are chains of steps: at least 64 rows (3,000 x 64 x 10: 17.6 us with
   // 256, 11.9; 128 for outputs whose partials take longer to add, 512 x 256: 25 and 22).
   const int64_t least = M * N <= 32768 ? 64 : 128;
-  const int64_t split = std::max<int64_t>(least, ceil_div(ceil_div(K, want), (int64_t)kKs) * kKs);
+  const int64_t split =
+      std::max<int64_t>(least, std::min(rows, ceil_div(ceil_div(K, want), (int64_t)kKs) * kKs));
   const int64_t chunks = ceil_div(K, split);
   float* part = nullptr;
   GCN_CHECK(talloc(&part, chunks * M * N, stream, "GEMM partials"));

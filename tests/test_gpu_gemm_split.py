@@ -321,3 +321,27 @@ def test_zero_sums_have_no_sign(G, op):
         C = G.gcn_gemm_f32(G.GCN_GEMM_NN, A, B)
     bits = C.view(torch.int32)
     assert torch.all(bits[::3] == 0) and torch.all(bits[:, 5::7] == 0)
+
+
+def _tn(M, N, K, seed):
+    import torch
+    gen = torch.Generator(device="cuda:0").manual_seed(seed)
+    A = torch.randn(K, M, device="cuda:0", generator=gen)
+    B = torch.randn(K, N, device="cuda:0", generator=gen)
+    ref = torch.zeros(M, N, device="cuda:0", dtype=torch.float64)
+    for k in range(0, K, 1 << 18):
+        ref += A[k:k + (1 << 18)].double().t().contiguous() @ B[k:k + (1 << 18)].double()
+    return A, B, ref
+
+
+# fp32 sums in chunks of 1024 rows leave 6.1e-7 (4 rows to a rounding); these
+# no more, at the sizes whose chunks are longest
+@pytest.mark.parametrize("M,N,K", [(512, 256, 500000), (300, 300, 500000), (1000, 1000, 20000),
+                                   (1000, 520, 100001), (516, 256, 1000003)])
+def test_tn_precision(G, M, N, K):
+    note("split tn precision %dx%dx%d" % (M, N, K))
+    A, B, ref = _tn(M, N, K, 380)
+    C = G.gcn_gemm_f32(G.GCN_GEMM_TN, A, B)
+    rel = ((C.double() - ref).norm() / ref.norm()).item()
+    note("rel %.2e" % rel)
+    assert rel <= 6.1e-7 if K < 1000000 else rel <= 8.7e-7  # 2048 rows there
