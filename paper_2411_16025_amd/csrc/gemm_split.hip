@@ -447,11 +447,12 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tall(TallArgs a) {
 struct TnArgs {
   int M, N;
   int64_t K, split, chunks;  // rows of a chunk (a multiple of 16), their number
+  int64_t run, groups;       // chunks that a workgroup sums, groups of so many chunks
   const float* A;
   int64_t lda;
   const float* B;
   int64_t ldb;
-  float* part;  // [chunks][M][N]
+  float* part;  // [groups][M][N]
   int m_tiles, n_tiles;
 };
 
@@ -459,8 +460,10 @@ struct TnArgs {
 // loads (32 lanes on neighbouring columns), which gives a thread the 8 k of
 // one operand lane; they are split and stored to LDS as such, PF steps after
 // their loads were issued (PF = 1 where the accumulators leave no registers for two).
-// A is negated in every other chunk (see the head of this file).
-template <int WR, int WC, int RBW, int NBW, int PF>
+// A is negated in every other chunk (see the head of this file). RUN: a workgroup
+// takes several chunks, one after the other, and adds their sums to its partial
+// C (without it the loop is gone, and with it the registers it costs).
+template <int WR, int WC, int RBW, int NBW, int PF, bool RUN>
 __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
   constexpr int RB = WR * RBW, NB = WC * NBW, NT = 64 * WR * WC;
   constexpr int AU = (RB * 64 + NT - 1) / NT;  // (column, half step) units per thread
@@ -468,16 +471,14 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
   __shared__ __align__(16) char lds[2][(RB + NB) * 3 * kFrag];
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wr = w / WC, wc = w % WC;
-  // the tiles of a chunk run on one XCD, one after the other: they read the
+  // the tiles of a group run on one XCD, one after the other: they read the
   // same rows of A and B
   const int tiles = a.m_tiles * a.n_tiles;
   const int64_t idx = blockIdx.x >> 3;
   const int tile = (int)(idx % tiles);
-  const int64_t chunk = idx / tiles * 8 + (blockIdx.x & 7);
-  if (chunk >= a.chunks) return;  // the whole workgroup
+  const int64_t group = idx / tiles * 8 + (blockIdx.x & 7);
+  if (group >= a.groups) return;  // the whole workgroup
   const int m0 = (tile / a.n_tiles) * RB * 32, n0 = (tile % a.n_tiles) * NB * 32;
-  const int64_t kb = chunk * a.split;
-  const int64_t ke = kb + a.split < a.K ? kb + a.split : a.K;
 
   // unit u of a block of columns: column (u / 64) * 32 + u % 32, half u / 32 % 2;
   // in operand order that is 16-byte slot u % 64 of block u / 64
@@ -486,125 +487,142 @@ __global__ __launch_bounds__(64 * WR * WC, 2) void k_split_tn(TnArgs a) {
 #pragma unroll
   for (int p = 0; p < AU; ++p) {
     const int u = t + p * NT, c = m0 + (u >> 6) * 32 + (u & 31);
-    ao[p] = (uint32_t)(8 * ((u >> 5) & 1)) * (uint32_t)a.lda + ((c < a.M ? c : a.M - 1) - m0);
+    ao[p] = 4 * ((uint32_t)(8 * ((u >> 5) & 1)) * (uint32_t)a.lda + ((c < a.M ? c : a.M - 1) - m0));
   }
 #pragma unroll
   for (int p = 0; p < BU; ++p) {
     const int u = t + p * NT, c = n0 + (u >> 6) * 32 + (u & 31);
-    bo[p] = (uint32_t)(8 * ((u >> 5) & 1)) * (uint32_t)a.ldb + ((c < a.N ? c : a.N - 1) - n0);
+    bo[p] = 4 * ((uint32_t)(8 * ((u >> 5) & 1)) * (uint32_t)a.ldb + ((c < a.N ? c : a.N - 1) - n0));
   }
   const int h8 = 8 * ((t >> 5) & 1);  // the half is the same for all of a thread's units
-  const float sign = chunk & 1 ? -kUp : kUp;
-  float down = chunk & 1 ? -kDown : kDown;
-  struct Pieces {
-    float a[AU][8], b[BU][8];
-  } v[PF];
-  auto load = [&](Pieces& v, int64_t k) {
-    const float *ar = a.A + k * a.lda + m0, *br = a.B + k * a.ldb + n0;
-    const bool full = k + kKs <= ke;  // else the last, partial step, or one past it (not used)
-    if (full) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-#pragma unroll
-        for (int p = 0; p < AU; ++p) v.a[p][j] = (ar + j * a.lda)[ao[p]];
-#pragma unroll
-        for (int p = 0; p < BU; ++p) v.b[p][j] = (br + j * a.ldb)[bo[p]];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const bool in = k + h8 + j < ke;
-#pragma unroll
-        for (int p = 0; p < AU; ++p) v.a[p][j] = in ? (ar + j * a.lda)[ao[p]] : 0.f;
-#pragma unroll
-        for (int p = 0; p < BU; ++p) v.b[p][j] = in ? (br + j * a.ldb)[bo[p]] : 0.f;
-      }
-    }
-  };
-  auto store = [&](char* buf, Pieces& v) {
-#pragma unroll
-    for (int p = 0; p < AU; ++p) {
-      const int u = t + p * NT;
-      u4 s[3];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v.a[p][j] *= sign;
-      split8(v.a[p], s);
-      u4* q = reinterpret_cast<u4*>(buf) + (u >> 6) * 3 * 64 + (u & 63);
-      if (RB * 64 % NT == 0 || u < RB * 64) { q[0] = s[0]; q[64] = s[1]; q[128] = s[2]; }
-    }
-#pragma unroll
-    for (int p = 0; p < BU; ++p) {
-      const int u = t + p * NT;
-      u4 s[3];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v.b[p][j] *= kUp;
-      split8(v.b[p], s);
-      u4* q = reinterpret_cast<u4*>(buf + RB * 3 * kFrag) + (u >> 6) * 3 * 64 + (u & 63);
-      if (NB * 64 % NT == 0 || u < NB * 64) { q[0] = s[0]; q[64] = s[1]; q[128] = s[2]; }
-    }
-  };
 
-  f16 acc[RBW][NBW];
+  auto sum_chunk = [&](int64_t chunk, bool add) {
+    const int64_t kb = chunk * a.split;
+    const int64_t ke = kb + a.split < a.K ? kb + a.split : a.K;
+    const float sign = chunk & 1 ? -kUp : kUp;
+    float down = chunk & 1 ? -kDown : kDown;
+    struct Pieces {
+      float a[AU][8], b[BU][8];
+    } v[PF];
+    auto load = [&](Pieces& v, int64_t k) {
+      const float *ar = a.A + k * a.lda + m0, *br = a.B + k * a.ldb + n0;
+      const bool full = k + kKs <= ke;  // else the last, partial step, or one past it (not used)
+      if (full) {
 #pragma unroll
-  for (int i = 0; i < RBW; ++i)
+        for (int j = 0; j < 8; ++j) {
 #pragma unroll
-    for (int j = 0; j < NBW; ++j)
+          for (int p = 0; p < AU; ++p) v.a[p][j] = *at_bytes(ar + j * a.lda, ao[p]);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  auto step = [&](int64_t k, char* cur, char* next, Pieces& vnext, Pieces& vload) {
-    load(vload, k + PF * kKs);
-    const bf8* as = reinterpret_cast<const bf8*>(cur) + wr * RBW * 3 * 64 + lane;
-    const bf8* bs = reinterpret_cast<const bf8*>(cur + RB * 3 * kFrag) + wc * NBW * 3 * 64 + lane;
-    mul_step<RBW, NBW, PF>(as, bs, acc);
-    store(next, vnext);
-    if (PF == 2) pipeline<RBW, NBW>();
-    __syncthreads();
-  };
-  load(v[0], kb);
-  if (PF == 2) load(v[PF - 1], kb + kKs);
-  store(lds[0], v[0]);
-  __syncthreads();
-  int64_t k = kb;
-  for (; k + kKs < ke; k += 2 * kKs) {
-    step(k, lds[0], lds[1], v[PF - 1], v[0]);
-    step(k + kKs, lds[1], lds[0], v[0], v[PF - 1]);
-  }
-  if (k < ke) step(k, lds[0], lds[1], v[PF - 1], v[0]);
-
-  float* part = a.part + chunk * a.M * a.N;
-  const int wm = m0 + wr * RBW * 32, wn = n0 + wc * NBW * 32;
-  if (not_finite<RBW, NBW>(acc)) {
-    down = 1.f;
-    auto load = [&](int64_t k, float (*x)[4], float (*y)[4]) {
+          for (int p = 0; p < BU; ++p) v.b[p][j] = *at_bytes(br + j * a.ldb, bo[p]);
+        }
+      } else {
 #pragma unroll
-      for (int i = 0; i < RBW; ++i) {
-        const int m = wm + i * 32 + (lane & 31);
-        const float* q = a.A + k * a.lda + (m < a.M ? m : a.M - 1);
+        for (int j = 0; j < 8; ++j) {
+          const bool in = k + h8 + j < ke;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[i][j] = k + j < ke ? q[j * a.lda] : 0.f;
-      }
+          for (int p = 0; p < AU; ++p) v.a[p][j] = in ? *at_bytes(ar + j * a.lda, ao[p]) : 0.f;
 #pragma unroll
-      for (int i = 0; i < NBW; ++i) {
-        const int n = wn + i * 32 + (lane & 31);
-        const float* q = a.B + k * a.ldb + (n < a.N ? n : a.N - 1);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) y[i][j] = k + j < ke ? q[j * a.ldb] : 0.f;
+          for (int p = 0; p < BU; ++p) v.b[p][j] = in ? *at_bytes(br + j * a.ldb, bo[p]) : 0.f;
+        }
       }
     };
-    mul_again<RBW, NBW>(kb, ke, load, acc);
-  }
+    auto store = [&](char* buf, Pieces& v) {
 #pragma unroll
-  for (int i = 0; i < RBW; ++i)
+      for (int p = 0; p < AU; ++p) {
+        const int u = t + p * NT;
+        u4 s[3];
 #pragma unroll
-    for (int j = 0; j < NBW; ++j) {
-      const int n = wn + j * 32 + (lane & 31);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = wm + i * 32 + result_row(e, lane);
-        if (m < a.M && n < a.N) part[(int64_t)m * a.N + n] = acc[i][j][e] * down;
+        for (int j = 0; j < 8; ++j) v.a[p][j] *= sign;
+        split8(v.a[p], s);
+        u4* q = reinterpret_cast<u4*>(buf) + (u >> 6) * 3 * 64 + (u & 63);
+        if (RB * 64 % NT == 0 || u < RB * 64) { q[0] = s[0]; q[64] = s[1]; q[128] = s[2]; }
       }
+#pragma unroll
+      for (int p = 0; p < BU; ++p) {
+        const int u = t + p * NT;
+        u4 s[3];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v.b[p][j] *= kUp;
+        split8(v.b[p], s);
+        u4* q = reinterpret_cast<u4*>(buf + RB * 3 * kFrag) + (u >> 6) * 3 * 64 + (u & 63);
+        if (NB * 64 % NT == 0 || u < NB * 64) { q[0] = s[0]; q[64] = s[1]; q[128] = s[2]; }
+      }
+    };
+
+    f16 acc[RBW][NBW];
+#pragma unroll
+    for (int i = 0; i < RBW; ++i)
+#pragma unroll
+      for (int j = 0; j < NBW; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+    auto step = [&](int64_t k, char* cur, char* next, Pieces& vnext, Pieces& vload) {
+      load(vload, k + PF * kKs);
+      const bf8* as = reinterpret_cast<const bf8*>(cur) + wr * RBW * 3 * 64 + lane;
+      const bf8* bs = reinterpret_cast<const bf8*>(cur + RB * 3 * kFrag) + wc * NBW * 3 * 64 + lane;
+      mul_step<RBW, NBW, PF>(as, bs, acc);
+      store(next, vnext);
+      if (PF == 2) pipeline<RBW, NBW>();
+      __syncthreads();
+    };
+    load(v[0], kb);
+    if (PF == 2) load(v[PF - 1], kb + kKs);
+    store(lds[0], v[0]);
+    __syncthreads();
+    int64_t k = kb;
+    for (; k + kKs < ke; k += 2 * kKs) {
+      step(k, lds[0], lds[1], v[PF - 1], v[0]);
+      step(k + kKs, lds[1], lds[0], v[0], v[PF - 1]);
     }
+    if (k < ke) step(k, lds[0], lds[1], v[PF - 1], v[0]);
+
+    float* part = a.part + group * a.M * a.N;
+    int wm = m0 + wr * RBW * 32, wn = n0 + wc * NBW * 32, N = a.N;
+    // (the addresses of the sums are formed here, not kept over the chunks)
+    if (RUN) asm volatile("" : "+s"(wm), "+s"(wn), "+s"(N));
+    if (not_finite<RBW, NBW>(acc)) {
+      down = 1.f;
+      auto load = [&](int64_t k, float (*x)[4], float (*y)[4]) {
+#pragma unroll
+        for (int i = 0; i < RBW; ++i) {
+          const int m = wm + i * 32 + (lane & 31);
+          const float* q = a.A + k * a.lda + (m < a.M ? m : a.M - 1);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) x[i][j] = k + j < ke ? q[j * a.lda] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < NBW; ++i) {
+          const int n = wn + i * 32 + (lane & 31);
+          const float* q = a.B + k * a.ldb + (n < a.N ? n : a.N - 1);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) y[i][j] = k + j < ke ? q[j * a.ldb] : 0.f;
+        }
+      };
+      mul_again<RBW, NBW>(kb, ke, load, acc);
+    }
+#pragma unroll
+    for (int i = 0; i < RBW; ++i)
+#pragma unroll
+      for (int j = 0; j < NBW; ++j) {
+        const int n = wn + j * 32 + (lane & 31);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int m = wm + i * 32 + result_row(e, lane);
+          if (m < a.M && n < N) {
+            float* q = part + (int64_t)m * N + n;
+            const float v = acc[i][j][e] * down;
+            *q = RUN && add ? *q + v : v;
+          }
+        }
+      }
+  };
+  if constexpr (RUN) {
+    const int64_t first = group * a.run;
+    for (int64_t c = first; c < first + a.run && c < a.chunks; ++c) sum_chunk(c, c != first);
+  } else {
+    sum_chunk(group, false);
+  }
 }
 
 }  // namespace
@@ -698,28 +716,34 @@ gcn_status gemm_split_tn(int64_t M, int64_t N, int64_t K, const float* A, int64_
   const int64_t split =
       std::max<int64_t>(least, std::min(rows, ceil_div(ceil_div(K, want), (int64_t)kKs) * kKs));
   const int64_t chunks = ceil_div(K, split);
+  // The partials take about the memory of those of `most` rows (at most 1.3 times
+  // it), or of 512 workgroups (134 MB), if that is more: a workgroup adds up several
+  // chunks (512 x 256 x 2.45M: 335 MB instead of 671, 3.69 ms instead of 3.66).
+  const int64_t run = std::max<int64_t>(
+      1, std::min(ceil_div(chunks * most - 3 * K / 10, K), chunks * tiles / 512));
+  const int64_t groups = ceil_div(chunks, run);
   float* part = nullptr;
-  GCN_CHECK(talloc(&part, chunks * M * N, stream, "GEMM partials"));
-  const TnArgs a{(int)M, (int)N, K, split, chunks, A, lda, B, ldb, part, (int)m_tiles,
+  GCN_CHECK(talloc(&part, groups * M * N, stream, "GEMM partials"));
+  const TnArgs a{(int)M, (int)N, K, split, chunks, run, groups, A, lda, B, ldb, part, (int)m_tiles,
                  (int)n_tiles};
-  const dim3 grid((unsigned)(tiles * ceil_div(chunks, (int64_t)8) * 8));
+  const dim3 grid((unsigned)(tiles * ceil_div(groups, (int64_t)8) * 8));
   hipError_t e;
   {
     ProfScope ps("gemm_tn_partial", stream);
-    auto go = [&](auto kern, int threads) {
-      hipLaunchKernelGGL(kern, grid, dim3(threads), 0, stream, a);
+    auto go = [&](auto kern, auto kern_run, int threads) {
+      hipLaunchKernelGGL(run > 1 ? kern_run : kern, grid, dim3(threads), 0, stream, a);
     };
     if (wide)
-      go(k_split_tn<4, 2, 2, 4, 1>, 512);
+      go(k_split_tn<4, 2, 2, 4, 1, false>, k_split_tn<4, 2, 2, 4, 1, true>, 512);
     else if (tn == 128)
-      go(k_split_tn<2, 2, 2, 2, 2>, 256);
+      go(k_split_tn<2, 2, 2, 2, 2, false>, k_split_tn<2, 2, 2, 2, 2, true>, 256);
     else if (tn == 64)
-      go(k_split_tn<4, 1, 1, 2, 2>, 256);
+      go(k_split_tn<4, 1, 1, 2, 2, false>, k_split_tn<4, 1, 1, 2, 2, true>, 256);
     else
-      go(k_split_tn<4, 1, 1, 1, 2>, 256);
+      go(k_split_tn<4, 1, 1, 1, 2, false>, k_split_tn<4, 1, 1, 1, 2, true>, 256);
     e = hipGetLastError();
   }
-  gcn_status st = e == hipSuccess ? sum_partials(M, N, chunks, part, C, ldc, stream)
+  gcn_status st = e == hipSuccess ? sum_partials(M, N, groups, part, C, ldc, stream)
                                   : hip_fail(e, "k_split_tn", __FILE__, __LINE__);
   tfree(part, stream);
   return st;

@@ -345,3 +345,28 @@ def test_tn_precision(G, M, N, K):
     rel = ((C.double() - ref).norm() / ref.norm()).item()
     note("rel %.2e" % rel)
     assert rel <= 6.1e-7 if K < 1000000 else rel <= 8.7e-7  # 2048 rows there
+
+
+def test_tn_partials(G):
+    """Chunks that one workgroup adds up: the same bits every time, a chunk with an
+    infinity among them, and the partial sums of no more than the fp32 kernel's
+    (598 chunks of 4,096 rows) kept afterwards."""
+    import torch
+    note("split tn partials")
+    M, N, K = 512, 256, 2449029
+    A, B, ref = _tn(M, N, K, 381)
+    C = torch.empty(M, N, device="cuda:0")
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    G.gcn_gemm_f32(G.GCN_GEMM_TN, A, B, C=C)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] <= 1.3 * 598 * M * N * 4
+    assert ((C.double() - ref).norm() / ref.norm()).item() <= 11.7e-7
+    C2 = G.gcn_gemm_f32(G.GCN_GEMM_TN, A, B)
+    assert torch.equal(C.view(torch.int32), C2.view(torch.int32))
+    A[2000000, 7] = float("inf")
+    C2 = G.gcn_gemm_f32(G.GCN_GEMM_TN, A, B)
+    assert torch.equal(C2[7], float("inf") * B[2000000].sign())
+    keep = torch.arange(M, device="cuda:0") != 7
+    # (the tiles of that chunk are summed on the fp32 instruction)
+    assert ((C2.double() - ref)[keep].norm() / ref[keep].norm()).item() <= 11.7e-7
