@@ -15,8 +15,9 @@
 // exact in the matrix core and are added to the fp32 accumulator sixteen at a time,
 // the small ones first. Against 64 bits, normal values, K = 100 / 256 / 516:
 // 1.5e-7 / 2.4e-7 / 3.5e-7 here, 1.8e-7 / 2.9e-7 / 4.1e-7 with
-// v_mfma_f32_16x16x4_f32; all operands 1.0038834, K = 16 / 256 / 1024: 5.9e-8 /
-// 1.8e-7 / 1.8e-7 and 5.9e-8 / 5.9e-8 / 1.5e-5.
+// v_mfma_f32_16x16x4_f32; all operands positive 1.2e-7 / 1.9e-7 / 2.7e-7 and 1.1e-7
+// / 1.7e-7 / 2.5e-7; all operands 1.0038834, K = 16 / 256 / 1024, 5.9e-8 / 1.8e-7 /
+// 1.8e-7 and 5.9e-8 / 5.9e-8 / 1.5e-5.
 //
 // Small operands. The parts of an fp32 number are multiples of 2^-149, its
 // smallest step, but a bf16 part below 2^-126 counts as 0 in the matrix core. So
@@ -41,9 +42,9 @@
 //
 // What bounds them: random operands hold the chip's bf16 matrix cores at about 1.1
 // PFLOP/s (an 8192^3 library product reaches 1.12), 185 TFLOP/s of fp32
-// products. 2,449,029 x 256 x 516: 3.61 ms, 179 TFLOP/s (5.57 ms on the fp32
-// instruction); x 512 x 256 transposed weights 3.60 ms (6.21); A^T B 512 x 256
-// 3.73 ms (5.51). Shallow products (K = 100: 1.31 ms, 1.61 before) are bound by
+// products. 2,449,029 x 256 x 516: 3.51 ms, 184 TFLOP/s (5.57 ms on the fp32
+// instruction); x 512 x 256 transposed weights 3.57 ms (6.21); A^T B 512 x 256
+// 3.57 ms (5.44). Shallow products (K = 100: 1.11 ms, 1.61 before) are bound by
 // writing C, which a tile cannot overlap with its own products.
 
 #include <algorithm>

@@ -4,12 +4,14 @@ Against float64 products of the same inputs, within 1e-5 of the sum of |terms|
 per element (a sum of K <= 4096 terms with one rounding per 16 of each of six
 part products is within 6 K / 16 * 2^-24 <= 9.2e-5 at the very worst, and
 rounding errors of either sign leave a few 1e-7), on both sides of the column,
-row and K tiles; and infinities and NaN where an fp32 product has them.
+row and K tiles; and infinities and NaN where an fp32 product has them. The masked and ReLU products,
+which only the training steps form, through the GCN step.
 """
 
 import numpy as np
 import pytest
 
+import oracle
 import synth
 from gpu_util import assert_close, dev, host, note
 
@@ -370,3 +372,38 @@ def test_tn_partials(G):
     keep = torch.arange(M, device="cuda:0") != 7
     # (the tiles of that chunk are summed on the fp32 instruction)
     assert ((C2.double() - ref)[keep].norm() / ref[keep].norm()).item() <= 11.7e-7
+
+
+# the unfused GCN step's dH1 = (dZ2 W2^T) masked (n x hidden x classes from 4e8 on) on
+# each tile width, whole and cut tiles, and H1 = relu(P W1) where it aggregates first
+@pytest.mark.parametrize("n,f_in,hidden,C", [(70001, 128, 128, 47), (100001, 132, 100, 47),
+                                             (45001, 200, 192, 47), (34001, 128, 256, 47),
+                                             (33001, 130, 250, 49)])
+def test_masked_in_the_gcn_step(G, n, f_in, hidden, C):
+    import torch
+    assert n * hidden * C >= 4e8 and hidden > 64
+    note("split masked, gcn step %s" % ((n, f_in, hidden, C),))
+    src, dst = synth.rmat_edges(391, n, 4 * n, perm_seed=392)
+    flags = synth.SYMMETRIZE | synth.ADD_SELF_LOOPS
+    X, y = synth.normal(393, n, f_in), synth.labels(394, n, C)
+    W1, W2 = synth.glorot(395, f_in, hidden), synth.glorot(396, hidden, C)
+    g = G.gcn_build_csr(n, n, dev(src), dev(dst), flags)
+    G.gcn_normalize(g)
+    loss, dW1, dW2 = G.gcn_gcn2_step(g, dev(X), dev(W1), dev(W2), dev(y))
+    torch.cuda.synchronize()
+    g.free()
+    og = oracle.Graph(n, n, src, dst, flags)
+    ref = oracle.gcn_step(og, X, W1, W2, y)
+    assert abs(float(loss) - ref["loss"]) <= 1e-5 * abs(ref["loss"])
+    agg_t = lambda T: oracle._agg64(og.csc_ptr, og.csc_idx, og.csc_val, T)
+    aX = np.abs(X).astype(np.float64)
+    S1 = aX.T @ agg_t(np.abs(ref["dH1"]))
+    S2 = np.abs(ref["H1"]).T @ agg_t(np.abs(ref["dlogits"]))
+    # a unit whose sum is within fp32 rounding of 0 (2e-6 of its terms' magnitudes:
+    # up to 200 products, then a row's entries) may pass its gradient or not
+    agg = lambda T: oracle._agg64(og.csr_ptr, og.csr_idx, og.csr_val, T)
+    near = np.abs(agg(X.astype(np.float64) @ W1)) <= 2e-6 * agg(aX @ np.abs(W1))
+    note("%d units at 0" % near.sum())
+    E1 = aX.T @ agg_t(np.abs(ref["dH1"]) * near)
+    assert np.all(np.abs(host(dW1) - ref["dW1"]) <= 1e-5 * S1 + E1)
+    assert_close(host(dW2), ref["dW2"], S2, what="dW2")
