@@ -241,8 +241,8 @@ def test_gcn_step_transform_first(G):
 
 
 def test_gcn_step_unaligned_inputs(G):
-    # f_in = 101: X rows are not 16-byte aligned, so layer 1 aggregates them
-    # on the scalar path before its product (P is stored padded to 104)
+    # f_in = 101: X rows are not 16-byte aligned, so layer 1 gathers them with
+    # unaligned loads before its product (P is stored padded to 104)
     note("gcn step unaligned inputs")
     n = 2000
     src, dst = synth.rmat_edges(215, n, 10 * n, perm_seed=216)
